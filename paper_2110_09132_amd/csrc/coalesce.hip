@@ -42,7 +42,8 @@
 // The lookup requests of the row-wise forward exchange reuse kernels 1-3 on
 // the owner-major keys and replace 4-5 by request_kernel (no rows to sum).
 // Batches of at most 2048 tokens take one kernel instead of all five
-// (small_coalesce_kernel: the same keys, sort and sums in one workgroup).
+// (small_coalesce_kernel: the same keys, sort and sums, every workgroup
+// sorting for itself and summing a slice of the columns).
 // The order of every floating-point addition depends only on the ids, never
 // on scheduling, so results are bitwise reproducible.
 #include <hip/hip_ext.h>
@@ -846,163 +847,179 @@ __global__ __launch_bounds__(kCombineThreads) void seg_combine_kernel(const floa
   }
 }
 
-// ------------------------------------------------------- one-workgroup path
-// Batches of at most kSmallMax tokens are coalesced by one workgroup in one
-// launch: the keys (built as in sort_keys_upsweep) are compacted to the
-// tokens that take part, sorted by an LSD radix sort in LDS (8-bit digits,
-// stable ranking as in the radix passes), and the segments are summed, each
-// by a group of lanes, over its tokens in sorted order.  The outputs are those
-// of the multi-kernel path; the fp32 sums of segments that would cross a
-// 32-token chunk there are rounded in another order (a plain sorted-order sum
-// here), within the same bound.  For small batches the launches and the gaps
-// between them are most of the multi-kernel path's time.
-constexpr int kSmallThreads = 1024;
-constexpr int kSmallItems = 2;
-constexpr int kSmallMax = kSmallThreads * kSmallItems;
+// ------------------------------------------------------------ small batches
+// Batches of at most 2048 tokens take one launch.  Each workgroup sorts the
+// whole batch for itself in LDS (an LSD radix sort with the stable ranking of
+// the radix passes; its first pass also drops the tokens that take no part)
+// and sums one slice of the columns, so that no workgroup waits for another;
+// the first one writes the ids, offsets and counts.  The slice of every row is
+// staged in LDS (64 KB for the most rows a workgroup sorts), all its loads in
+// flight at once; then each segment's rows are added in sorted order, one lane
+// per column vector, so a hot row costs LDS reads and not round trips to
+// memory.  The outputs are those of the multi-kernel path; the fp32 sums of
+// segments that would cross a 32-token chunk there are rounded in another
+// order (a plain sorted-order sum here), within the same bound.
+// What bounds it is latency: about 2 us per sort pass, then one round trip.
+// Measured per training step of 2000 tokens with rows of 1024 floats: 299 us
+// with one workgroup summing every column (the kernel 276 us), 43 us with
+// a workgroup per slice; 512 tokens of 64 floats, the kernel: 12.9 -> 10.2 us.
+constexpr int kSmallMax = 2048;
 constexpr int kSmallGroupsMax = 2 * 1024;  // owner groups, times two with the split
+constexpr int kSmallDigit = 9;             // bits per pass in LDS, at most
+constexpr int kSmallStage = 64 * 1024;     // bytes of LDS for the rows' slices
+constexpr int kSmallUnroll = 8;            // staged rows read together per segment
+constexpr int kSmallMaxBlocks = 2048;      // workgroups per launch (wider rows loop); a multiple of the XCDs
+constexpr int kXcds = 8;
 
-template <bool BF16, int VEC>
-__global__ __launch_bounds__(kSmallThreads) void small_coalesce_kernel(
-    const int32_t* __restrict__ ids, int T, KeySpec ks, int npass, const void* __restrict__ grad, int D, int log2L,
+// Vectors of one row's slice: what the staging area holds for `rows` rows.
+constexpr int small_slice(int rows, int vec) { return kSmallStage / (rows * vec * static_cast<int>(sizeof(float))); }
+
+template <bool BF16, int VEC, int NT, int IT>
+__global__ __launch_bounds__(NT) void small_coalesce_kernel(
+    const int32_t* __restrict__ ids, int T, KeySpec ks, int npass, int bits, const void* __restrict__ grad, int D,
     int32_t* __restrict__ uniq_ids, int32_t* __restrict__ seg_offsets, int32_t* __restrict__ num_unique,
     float* __restrict__ uniq_grad, int32_t* __restrict__ group_counts, int32_t* __restrict__ group_offsets,
     int32_t* status) {
-  constexpr int NT = kSmallThreads, NW = NT / kWave, IT = kSmallItems;
-  __shared__ uint32_t key_s[2][kSmallMax];
-  __shared__ int32_t pos_s[2][kSmallMax];
-  __shared__ uint32_t cnt[NW * 256];
-  __shared__ uint32_t dstart[256];
+  constexpr int NW = NT / kWave, kMax = NT * IT, kBins = 1 << kSmallDigit;
+  using Row = GradRow<BF16, VEC>;
+  using Acc = typename Row::Acc;
+  constexpr int L = small_slice(kMax, VEC);
+  static_assert(NW * kBins * sizeof(uint32_t) <= kSmallStage, "the sort's counters fit the staging area");
+  static_assert(NT % L == 0 && kMax * L * sizeof(Acc) == kSmallStage, "whole rows per staging round");
+  __shared__ __align__(16) unsigned char stage_s[kSmallStage];  // the sort's counters, then the rows' slices
+  __shared__ uint32_t key_s[2][kMax];
+  __shared__ int32_t pos_s[2][kMax];
+  __shared__ uint32_t dstart[kBins];
   __shared__ uint32_t wsum[NW];
-  __shared__ uint32_t hs[kSmallMax];              // head flags, then their exclusive scan
-  __shared__ int32_t sstart[kSmallMax + 1];       // first sorted token of each segment, and n
-  __shared__ int32_t goff[kSmallGroupsMax + 1];   // group offsets
+  __shared__ uint32_t hs[kMax];                  // head flags, then their exclusive scan
+  __shared__ int32_t sstart[kMax + 1];           // first sorted token of each segment, and n
+  __shared__ int32_t goff[kSmallGroupsMax + 1];  // group offsets (first workgroup)
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(stage_s);
+  Acc* stage = reinterpret_cast<Acc*>(stage_s);
   const int w = threadIdx.x / kWave;
   const int lane = static_cast<int>(lane_id());
+  const bool meta = blockIdx.x == 0;
   const int Tc = ks.count_dev != nullptr ? min(max(*ks.count_dev, 0), T) : T;  // tokens that exist
   // 1. keys of the tokens, element e = (wave, round, lane) as the ranking walks them
   uint32_t key[IT], dig[IT], lpos[IT];
-  bool inb[IT], take[IT];
+  int32_t pos[IT];
+  bool valid[IT];
+  int32_t id[IT];
   bool bad_id = false, bad_owner = false;
 #pragma unroll
   for (int r = 0; r < IT; ++r) {
-    const int e = w * IT * kWave + r * kWave + lane;
-    inb[r] = e < Tc;
-    const int32_t id = ids[min(e, T - 1)];
-    const bool idok = id >= 0 && static_cast<uint32_t>(id) < ks.V;
-    uint32_t own = 0;
-    if (ks.row_owner != nullptr) own = static_cast<uint32_t>(ks.row_owner[idok ? id : 0]);
-    const bool ownok = own < static_cast<uint32_t>(ks.P);
-    take[r] = inb[r] && idok && ownok;
-    bad_id |= inb[r] && !idok;
-    bad_owner |= inb[r] && idok && !ownok;
-    key[r] = (own << ks.ib) | static_cast<uint32_t>(idok ? id : 0);
-    if (ks.next_tab != nullptr && take[r] && !in_next(static_cast<uint32_t>(id), ks)) key[r] |= 1u << ks.cls_shift;
-    dig[r] = take[r] ? 0u : 1u;
+    pos[r] = w * IT * kWave + r * kWave + lane;
+    id[r] = ids[min(pos[r], T - 1)];
   }
-  if (__any(bad_id) && lane == 0) raise_flag(status, EMB_DEV_ID_OUT_OF_RANGE);
-  if (__any(bad_owner) && lane == 0) raise_flag(status, EMB_DEV_OWNER_OUT_OF_RANGE);
-  // 2. the tokens that take part, first and in token order
-  (void)tile_stable_rank<NT, IT>(dig, inb, 2, 1, cnt, dstart, wsum, lpos);
-  const int n = static_cast<int>(dstart[1]);  // tokens that take part
 #pragma unroll
   for (int r = 0; r < IT; ++r) {
-    if (take[r]) {
-      key_s[0][lpos[r]] = key[r];
-      pos_s[0][lpos[r]] = w * IT * kWave + r * kWave + lane;
-    }
+    const bool inb = pos[r] < Tc;
+    const bool idok = id[r] >= 0 && static_cast<uint32_t>(id[r]) < ks.V;
+    uint32_t own = 0;
+    if (ks.row_owner != nullptr) own = static_cast<uint32_t>(ks.row_owner[idok ? id[r] : 0]);
+    const bool ownok = own < static_cast<uint32_t>(ks.P);
+    valid[r] = inb && idok && ownok;
+    bad_id |= inb && !idok;
+    bad_owner |= inb && idok && !ownok;
+    key[r] = (own << ks.ib) | static_cast<uint32_t>(idok ? id[r] : 0);
+    if (ks.next_tab != nullptr && valid[r] && !in_next(static_cast<uint32_t>(id[r]), ks)) key[r] |= 1u << ks.cls_shift;
   }
-  __syncthreads();
-  // 3. LSD radix passes of 8-bit digits in LDS
-  int cur = 0;
+  if (meta && __any(bad_id) && lane == 0) raise_flag(status, EMB_DEV_ID_OUT_OF_RANGE);
+  if (meta && __any(bad_owner) && lane == 0) raise_flag(status, EMB_DEV_OWNER_OUT_OF_RANGE);
+  // 2. LSD radix passes in LDS; the first ranks only the tokens that take part
+  const uint32_t dmask = (1u << bits) - 1u;
+  int cur = 0, n = 0;
   for (int p = 0; p < npass; ++p) {
-    bool valid[IT];
-    int32_t pos[IT];
+    if (p > 0) {
 #pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      const int e = w * IT * kWave + r * kWave + lane;
-      valid[r] = e < n;
-      key[r] = key_s[cur][min(e, kSmallMax - 1)];
-      pos[r] = pos_s[cur][min(e, kSmallMax - 1)];
-      dig[r] = valid[r] ? (key[r] >> (8 * p)) & 255u : 0u;
+      for (int r = 0; r < IT; ++r) {
+        const int e = w * IT * kWave + r * kWave + lane;
+        valid[r] = e < n;
+        key[r] = key_s[cur][e];
+        pos[r] = pos_s[cur][e];
+      }
     }
-    (void)tile_stable_rank<NT, IT>(dig, valid, 256, 8, cnt, dstart, wsum, lpos);
+#pragma unroll
+    for (int r = 0; r < IT; ++r) dig[r] = valid[r] ? (key[r] >> (bits * p)) & dmask : 0u;
+    n = static_cast<int>(tile_stable_rank<NT, IT, kSmallDigit>(dig, valid, 1 << bits, bits, cnt, dstart, wsum, lpos));
+    cur ^= 1;
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
       if (valid[r]) {
-        key_s[cur ^ 1][lpos[r]] = key[r];
-        pos_s[cur ^ 1][lpos[r]] = pos[r];
+        key_s[cur][lpos[r]] = key[r];
+        pos_s[cur][lpos[r]] = pos[r];
       }
     }
-    cur ^= 1;
     __syncthreads();
   }
   const uint32_t* sk = key_s[cur];
   const int32_t* sp = pos_s[cur];
-  // 4. segments: heads, unique indices, ids, starts, offsets of the owner groups
+  // 3. segments: heads, unique indices, starts; the first workgroup writes them
+  // with the ids and the offsets of the owner groups
   for (int e = threadIdx.x; e < n; e += NT) hs[e] = (e == 0 || sk[e] != sk[e - 1]) ? 1u : 0u;
   __syncthreads();
   const int U = static_cast<int>(block_exclusive_scan<NT>(hs, n, wsum));
   for (int e = threadIdx.x; e < n; e += NT) {
     if (e > 0 && sk[e] == sk[e - 1]) continue;  // not a head
     const int u = static_cast<int>(hs[e]);
+    sstart[u] = e;
+    if (!meta) continue;
     uniq_ids[u] = static_cast<int32_t>(sk[e] & ks.id_mask);
     seg_offsets[u] = e;
-    sstart[u] = e;
     const int o = min(group_of(sk[e], ks), ks.G);  // groups o_prev < q <= o start at this row
     const int o_prev = e == 0 ? -1 : group_of(sk[e - 1], ks);
     for (int q = o_prev + 1; q <= o; ++q) goff[q] = u;
   }
   if (threadIdx.x == 0) {
-    seg_offsets[U] = n;
     sstart[U] = n;
-    num_unique[0] = U;
-    const int o_last = n > 0 ? min(group_of(sk[n - 1], ks), ks.G) : -1;
-    for (int q = o_last + 1; q <= ks.G; ++q) goff[q] = U;
+    if (meta) {
+      seg_offsets[U] = n;
+      num_unique[0] = U;
+      const int o_last = n > 0 ? min(group_of(sk[n - 1], ks), ks.G) : -1;
+      for (int q = o_last + 1; q <= ks.G; ++q) goff[q] = U;
+    }
   }
   __syncthreads();
-  if (group_offsets != nullptr)
+  if (meta && group_offsets != nullptr)
     for (int q = threadIdx.x; q <= ks.G; q += NT) {
       group_offsets[q] = goff[q];
       if (q < ks.G) group_counts[q] = goff[q + 1] - goff[q];
     }
-  // 5. the sums: L lanes per segment, each segment's rows in sorted order
-  using Row = GradRow<BF16, VEC>;
-  using Acc = typename Row::Acc;
+  // 4. the sums of this workgroup's column slices.  Workgroups are handed to the
+  // XCDs in turn; neighbouring slices, which share cache lines, go to one XCD.
+  if (n == 0) return;
   const int Dv = D / VEC;
-  const int L = 1 << log2L;
-  const int rpw = kWave >> log2L;
-  const int sub = lane >> log2L;
-  const int cl = lane & (L - 1);
+  const int nslices = (Dv + L - 1) / L;
+  const int per_xcd = (nslices + kXcds - 1) / kXcds;
+  const int x = static_cast<int>(blockIdx.x) % kXcds;
+  const int cl = static_cast<int>(threadIdx.x) % L;
+  const int grp = static_cast<int>(threadIdx.x) / L;
   Acc* out = reinterpret_cast<Acc*>(uniq_grad);
-  for (int u = w * rpw + sub; u < U; u += NW * rpw) {
-    const int S = sstart[u], E = sstart[u + 1];
-    for (int cb = 0; cb < Dv; cb += L) {
-      const int c = cb + cl;
-      if (c >= Dv) continue;
+  for (int i = static_cast<int>(blockIdx.x) / kXcds; i < per_xcd; i += static_cast<int>(gridDim.x) / kXcds) {
+    const int c = (x * per_xcd + i) * L + cl;
+    if (c - cl >= Dv) break;  // past the last slice (uniform)
+    const int cc = min(c, Dv - 1);
+    Acc g[IT * L];
+#pragma unroll
+    for (int k = 0; k < IT * L; ++k)
+      g[k] = Row::load(grad, static_cast<size_t>(sp[min(grp + k * (NT / L), n - 1)]), Dv, cc);
+#pragma unroll
+    for (int k = 0; k < IT * L; ++k) stage[static_cast<int>(threadIdx.x) + k * NT] = g[k];
+    __syncthreads();
+    for (int u = grp; u < U; u += NT / L) {
+      const int S = sstart[u], E = sstart[u + 1];
       Acc acc = Acc{};
-      int i = S;
-      // eight rows in flight, added in order (a hot segment's chain of round trips is the
-      // longest part of the kernel: 512 Zipf tokens, 14.2 -> 12.8 us with eight instead of four)
-      for (; i + 8 <= E; i += 8) {
-        Acc g[8];
+      for (int e = S; e < E; e += kSmallUnroll) {
+        Acc v[kSmallUnroll];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) g[k] = Row::load(grad, static_cast<size_t>(sp[i + k]), Dv, c);
+        for (int k = 0; k < kSmallUnroll; ++k) v[k] = stage[min(e + k, E - 1) * L + cl];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) acc += g[k];
+        for (int k = 0; k < kSmallUnroll; ++k)
+          if (e + k < E) acc += v[k];
       }
-      for (; i + 4 <= E; i += 4) {  // four rows in flight, added in order
-        const Acc g0 = Row::load(grad, static_cast<size_t>(sp[i]), Dv, c);
-        const Acc g1 = Row::load(grad, static_cast<size_t>(sp[i + 1]), Dv, c);
-        const Acc g2 = Row::load(grad, static_cast<size_t>(sp[i + 2]), Dv, c);
-        const Acc g3 = Row::load(grad, static_cast<size_t>(sp[i + 3]), Dv, c);
-        acc += g0;
-        acc += g1;
-        acc += g2;
-        acc += g3;
-      }
-      for (; i < E; ++i) acc += Row::load(grad, static_cast<size_t>(sp[i]), Dv, c);
-      out[static_cast<size_t>(u) * Dv + c] = acc;
+      if (c < Dv) out[static_cast<size_t>(u) * Dv + c] = acc;
     }
+    __syncthreads();  // the next slice overwrites the staged rows
   }
 }
 
@@ -1241,7 +1258,13 @@ bool coalesce_by_owner_supported(int64_t V, int P, bool split) {
 
 namespace {
 
-// Batches the one-workgroup kernel coalesces (its groups fit its LDS table).
+// Workgroups of the small-batch kernel: one per slice of L vectors, a multiple of the XCDs.
+unsigned small_blocks(int Dv, int L) {
+  const int per_xcd = ((Dv + L - 1) / L + kXcds - 1) / kXcds;
+  return grid_for(static_cast<long long>(per_xcd) * kXcds, kSmallMaxBlocks);
+}
+
+// Batches that one launch coalesces (their groups fit its LDS table).
 bool small_batch(int T, const KeySpec& ks) { return T <= kSmallMax && ks.G <= kSmallGroupsMax; }
 
 // full: the radix passes and head counts even for a small batch (the lookup
@@ -1265,7 +1288,7 @@ hipError_t sort_chain(const int32_t* ids, int T, int64_t V, int D, const Coalesc
     ks.next_bytemap = ws.tab_bytemap;
     ks.tab_shift = ws.tab_shift;
   }
-  // a small batch is sorted and summed by the one-workgroup kernel of the reduction half
+  // a small batch is sorted and summed by one kernel of the reduction half
   if (!full && small_batch(T, ks)) return hipGetLastError();
   // 1-3. the key of every token (owner and next-batch lookups once) with the digit
   // histograms of all passes, then the radix passes over (key, position)
@@ -1308,7 +1331,7 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
                           num_unique, group_counts, group_offsets, ks.G);
     return hipGetLastError();
   }
-  if (small_batch(T, ks)) {  // sort and sums in one workgroup (the sort half built only the next-id set)
+  if (small_batch(T, ks)) {  // sort and sums in one launch (the sort half built only the next-id set)
     const CoalesceWs wsn = carve(workspace, T, D, is_split(var) ? var.T_next : -1, V);
     KeySpec kss = ks;
     kss.count_dev = var.count_dev;
@@ -1317,14 +1340,27 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
       kss.next_bytemap = wsn.tab_bytemap;
       kss.tab_shift = wsn.tab_shift;
     }
-    const int npass = (max(key_bits(V, var.row_owner != nullptr, var.P, is_split(var)), 1) + 7) / 8;
+    const int B = max(key_bits(V, var.row_owner != nullptr, var.P, is_split(var)), 1);
+    const int npass = (B + kSmallDigit - 1) / kSmallDigit;
+    const int bits = (B + npass - 1) / npass;
     const bool v4 = (D % 4 == 0) && (reinterpret_cast<uintptr_t>(grad) % (grad_bf16 ? 8 : 16) == 0) &&
                     (reinterpret_cast<uintptr_t>(uniq_grad) % 16 == 0);
-    const int log2L = row_lanes_for(v4 ? D / 4 : D).log2_lanes;
-#define EMB_SMALL(BF, VC)                                                                                           \
-  hipExtLaunchKernelGGL((small_coalesce_kernel<BF, VC>), dim3(1), dim3(kSmallThreads), 0, stream, nullptr, done, 0, \
-                        ids, T, kss, npass, grad, D, log2L, uniq_ids, seg_offsets, num_unique, uniq_grad,  \
-                        group_counts, group_offsets, status)
+    const int Dv = v4 ? D / 4 : D;
+    // the fewest threads and keys per thread that hold the batch: shorter passes
+#define EMB_SMALL_N(BF, VC, NTH, ITM)                                                                               \
+  hipExtLaunchKernelGGL((small_coalesce_kernel<BF, VC, NTH, ITM>), dim3(small_blocks(Dv, small_slice(NTH * ITM, VC))), \
+                        dim3(NTH), 0, stream, nullptr, done, 0, ids, T, kss, npass, bits, grad, D, uniq_ids,        \
+                        seg_offsets, num_unique, uniq_grad, group_counts, group_offsets, status)
+#define EMB_SMALL(BF, VC)               \
+  do {                                  \
+    if (T <= 512)                       \
+      EMB_SMALL_N(BF, VC, 512, 1);      \
+    else if (T <= 1024)                 \
+      EMB_SMALL_N(BF, VC, 1024, 1);     \
+    else                                \
+      EMB_SMALL_N(BF, VC, 1024, 2);     \
+  } while (0)
+    static_assert(kSmallMax == 1024 * 2, "the largest small batch fits its kernel");
     if (v4) {
       if (grad_bf16)
         EMB_SMALL(true, 4);
@@ -1337,6 +1373,7 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
         EMB_SMALL(false, 1);
     }
 #undef EMB_SMALL
+#undef EMB_SMALL_N
     return hipGetLastError();
   }
   CoalesceWs ws = carve(workspace, T, D, -1, V);  // the next-id set, if any, lies past everything used here
