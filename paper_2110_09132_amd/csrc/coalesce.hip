@@ -6,13 +6,17 @@
 // over the gradient rows.
 //
 // Kernels (one stream, no host synchronisation):
-//  1. sort_keys_upsweep: the sort key of every token (owner and next-batch
+//  1-3. The tokens sorted by (key, position), and the number of first tokens of
+//     an id (heads) in each run of 128 sorted tokens.  Tokens whose id (or
+//     owner) is out of range take no part: they are not in the sorted sequence,
+//     which holds the n_valid tokens that do.  Batches of at most 655360 tokens
+//     take the bucket sort (bucket_sort.hip: two or three launches); larger
+//     ones a radix sort:
+//     sort_keys_upsweep: the sort key of every token (owner and next-batch
 //     lookups done once) and the digit histograms of every radix pass at once
 //     (the digit totals do not depend on the order of the keys); it also
-//     clears the look-back state used by the later kernels.  Tokens whose id
-//     (or owner) is out of range take no part: they are left out of the
-//     histograms and so out of the sorted sequence.
-//  2. sort_pass, once per digit of the key bits (<= 8 bits each, 9 where that
+//     clears the look-back state used by the later kernels.
+//     sort_pass, once per digit of the key bits (<= 8 bits each, 9 where that
 //     saves a pass): a stable LSD radix pass over (key, token position).
 //     Each tile ranks its keys in LDS with wave ballots, publishes its
 //     per-digit counts (before the ranking, so that the tiles after it find
@@ -22,10 +26,8 @@
 //     tiles, once done, leave the digit starts of the later passes, which then
 //     read one word per digit instead of every histogram.
 //     Tiles take their index from a ticket counter, so a tile only waits for
-//     tiles that are already running.  The sorted sequence holds the n_valid
-//     tokens that take part.
-//  3. seg_count: the number of first tokens of an id (heads) in each run of
-//     128 sorted tokens.
+//     tiles that are already running.
+//     seg_count: the heads.
 //  4. seg_reduce: each wave owns 32 consecutive sorted tokens (for batches of
 //     few tokens with wide rows, several workgroups share them, each summing
 //     a slice of the columns).  It finds the
@@ -50,6 +52,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "sort_keys.h"
 
 namespace emb {
 namespace {
@@ -58,23 +61,13 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kMaxPasses = 4;  // up to 31 key bits
 
-// Radix configuration: sort tiles on 512 threads, of 1024 keys (two per
-// thread), or of 1536 keys (three per thread) for batches of more than 32768
-// tokens; key-build tiles of 1024 tokens (two per thread); digits of at most
-// 8 bits, or 9 bits where that saves a pass (keys of 9, 17-18 or 25-27 bits:
-// one, two or three passes instead of two, three or four).  The passes are
-// latency-bound (a few dozen tiles on 256 CUs), so short per-thread chains win:
-// measured per owner-major call against 256-thread tiles of 2048 keys with
-// 2048-token key-build tiles, 4.5 to 8.8 us less on every workload (72.6 ->
-// 68.2 us for 65536 tokens of 24-bit keys); 1024 threads, or 4096- and
-// 8192-token key-build tiles, were slower.  Once only pass 0 summed the key
-// build's histograms, 1024-token key-build tiles gained up to 1.8 us more.
-// The look-back of a tile reads its predecessors 16 at a time from beyond
-// L2, so on 65536 tokens fewer, larger tiles pay (three keys per thread: 60.5
-// -> 58.7 us; four: 59.0), while on 16384 tokens they cost 1 to 2 us.  (Two
-// passes of 11-bit digits were measured slower than three of 8 bits for
-// 24-bit keys: the 2048-bin ranking is LDS-bound and runs on half as many
-// tiles.)
+// Radix configuration: sort tiles of 1536 keys on 512 threads (three per
+// thread); key-build tiles of 1024 tokens (two per thread); digits of at most 8
+// bits, or 9 bits where that saves a pass (keys of 9, 17-18 or 25-27 bits: one,
+// two or three passes instead of two, three or four).  The look-back of a tile
+// reads its predecessors 16 at a time from beyond L2, so fewer, larger tiles
+// pay on large batches (58.7 us per owner-major call of 65536 tokens against
+// 60.5 with two keys per thread; four: 59.0).
 template <int NT, int BITS, int ITEMS>
 struct SortCfg {
   static constexpr int kNT = NT;
@@ -86,22 +79,19 @@ struct SortCfg {
   static constexpr int kPasses = kMaxPasses;     // most passes this configuration runs
   static_assert(kUpTile % NT == 0, "whole key-build rounds");
 };
-using Narrow = SortCfg<512, 8, 2>;
-using Wide9 = SortCfg<512, 9, 2>;
-using NarrowBig = SortCfg<512, 8, 3>;
-using Wide9Big = SortCfg<512, 9, 3>;
-constexpr int kBigTileAbove = 32768;  // batches of more tokens take the 1536-key tiles
+using Narrow = SortCfg<512, 8, 3>;
+using Wide9 = SortCfg<512, 9, 3>;
 constexpr int kWide9Passes = 3;  // most passes of 9-bit digits
 // Histogram and look-back words per tile, for every pass of either configuration.
 constexpr int kHistPerTile = kMaxPasses * Narrow::kBins > kWide9Passes * Wide9::kBins ? kMaxPasses * Narrow::kBins
                                                                                       : kWide9Passes * Wide9::kBins;
-// The workspace is laid out for the configuration with the most tiles.
-static_assert(Narrow::kTile == Wide9::kTile && Narrow::kTile <= NarrowBig::kTile && Narrow::kTile <= Wide9Big::kTile,
-              "the workspace's tile count is the largest");
-static_assert(Narrow::kUpTile == Wide9::kUpTile && Narrow::kUpTile == NarrowBig::kUpTile &&
-              Narrow::kUpTile == Wide9Big::kUpTile, "one key-build tiling");
+// The workspace holds these words once per 1024 tokens for the histograms and
+// once for the look-back, whichever sort runs.
+constexpr int kWsTile = 1024;
+static_assert(kWsTile <= Narrow::kTile && kWsTile <= Wide9::kTile, "a region share per sort tile");
+static_assert(kWsTile == Narrow::kUpTile && kWsTile == Wide9::kUpTile, "a region share per key-build tile");
 constexpr int kChunk = 32;                    // sorted tokens per reduction wave
-constexpr int kRedTile = kChunk * kWaves;     // sorted tokens per reduction workgroup
+static_assert(kRedTile == kChunk * kWaves, "a reduction workgroup's waves share its tokens");
 constexpr int kLoadsInFlight = 8;
 // The combine of ids that cross reduction workgroups: one workgroup per such
 // id, its waves splitting the id's pieces (one per reduction workgroup it
@@ -124,48 +114,6 @@ __device__ __forceinline__ void publish(uint32_t* p, uint32_t v) {
 }
 __device__ __forceinline__ uint32_t peek(uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// How a token's id becomes its sort key: the id itself; with row owners,
-// owner << ib | id, which orders tokens by owner shard and by id inside it;
-// with the vertical split as well, class << (ib + ob) | owner << ib | id, where
-// class 0 marks the prior rows (the id occurs in the next batch) and 1 the
-// delayed ones, so that the prior rows of every owner come first.
-struct KeySpec {
-  uint32_t V;                // ids in [0, V) take part
-  const int32_t* row_owner;  // nullptr: the key is the id
-  int32_t P;                 // owners in [0, P) take part
-  int ib, ob;                // id bits and owner bits of a composite key
-  uint32_t id_mask;          // key -> id
-  uint32_t omask;            // (key >> ib) & omask -> owner
-  int cls_shift;             // key >> cls_shift -> class (32: no class bit)
-  const uint32_t* next_tab;  // set of the next batch's ids (nullptr: no split): one byte per
-                             // row of [0, V) (next_bytemap), else a hash set of 2^(32 - tab_shift) slots
-  bool next_bytemap;
-  int tab_shift;
-  int G;                     // groups of the output: owners, times 2 with the split
-  const int32_t* count_dev;  // if given: only the first *count_dev tokens take part
-};
-
-__device__ __forceinline__ int group_of(uint32_t key, const KeySpec& ks) {
-  const int cls = static_cast<int>(static_cast<uint64_t>(key) >> ks.cls_shift);
-  return cls * ks.P + static_cast<int>((key >> ks.ib) & ks.omask);
-}
-
-// Open-addressing hash set of ids (slot value id + 1, 0 = empty, linear probing).
-__device__ __forceinline__ uint32_t tab_slot(uint32_t id, int shift) { return (id * 0x9E3779B1u) >> shift; }
-
-__device__ __forceinline__ bool in_next(uint32_t id, const KeySpec& ks) {
-  if (ks.next_bytemap) return reinterpret_cast<const uint8_t*>(ks.next_tab)[id] != 0;
-  const uint32_t mask = 0xFFFFFFFFu >> ks.tab_shift;
-  uint32_t slot = tab_slot(id, ks.tab_shift);
-  for (uint32_t probe = 0; probe <= mask; ++probe) {
-    const uint32_t v = ks.next_tab[slot];
-    if (v == id + 1) return true;
-    if (v == 0) return false;
-    slot = (slot + 1) & mask;
-  }
-  return false;
 }
 
 __global__ __launch_bounds__(kThreads) void tab_clear_kernel(uint32_t* __restrict__ tab, int n) {
@@ -1153,19 +1101,17 @@ constexpr int64_t kBytemapMaxRows = int64_t{1} << 24;
 // The layout does not depend on the number of radix passes (sized for the
 // most), so one size serves the plain and the owner-major call; the split
 // appends its hash set (T_next < 0: none).
-template <class C>
-CoalesceWs carve_with(void* base, int T, int D, int T_next, int64_t V) {
+CoalesceWs carve(void* base, int T, int D, int T_next, int64_t V) {
   Carver cv{static_cast<char*>(base)};
   const size_t n = static_cast<size_t>(T);
-  const size_t ntiles = (n + C::kTile - 1) / C::kTile;
-  const size_t nup = (n + C::kUpTile - 1) / C::kUpTile;
+  const size_t ntiles = (n + kWsTile - 1) / kWsTile;
   const size_t nred = (n + kRedTile - 1) / kRedTile;
   CoalesceWs w;
   w.keys_a = cv.take<uint32_t>(n);
   w.keys_b = cv.take<uint32_t>(n);
   w.vals_a = cv.take<int32_t>(n);
   w.vals_b = cv.take<int32_t>(n);
-  w.up_hist = cv.take<uint32_t>(nup * kHistPerTile);
+  w.up_hist = cv.take<uint32_t>(ntiles * kHistPerTile);
   w.tickets = cv.take<uint32_t>(kMaxPasses);
   w.span_count = cv.take<int32_t>(1);
   w.sort_lb = cv.take<uint32_t>(static_cast<size_t>(kHistPerTile) * ntiles);
@@ -1193,7 +1139,30 @@ CoalesceWs carve_with(void* base, int T, int D, int T_next, int64_t V) {
   return w;
 }
 
-CoalesceWs carve(void* base, int T, int D, int T_next, int64_t V) { return carve_with<Narrow>(base, T, D, T_next, V); }
+// Batches the bucket sort takes: all that its buckets (of 4096 tokens at most in
+// LDS) hold with room to spare.  Lookup requests of T tokens, uniform and
+// Zipf(1.3) ids of 2^20 rows, radix -> bucket sort: 300: 27 -> 19 us; 16384:
+// 30.3 -> 20.5 and 30.8 -> 20.4; 65536: 36.0 -> 20.2 and 38.3 -> 22.8; 131072:
+// 44.4 -> 28.2 and 44.5 -> 33.8; 262144: 57 -> 40 and 59 -> 42; 524288: 92 -> 67
+// and 93 -> 65; 655360: 111 -> 75 and 112 -> 67; at 2^20 uniform tokens, where
+// buckets start to overflow, 175 -> 181.
+bool bucket_sorted(int T) { return T <= kBucketMaxTokens; }
+
+// The bucket sort's arrays, in the regions that the radix passes use (at least
+// 1.5 words per token each): the long buckets' keys and its own words share one.
+BucketWs bucket_ws(const CoalesceWs& w) {
+  BucketWs b{};
+  b.tile_keys = w.keys_b;
+  b.tile_vals = reinterpret_cast<uint32_t*>(w.vals_b);
+  b.keys = w.keys_a;
+  b.vals = reinterpret_cast<uint32_t*>(w.vals_a);
+  b.tmp_vals = w.up_hist;
+  b.tmp_keys = w.sort_lb;
+  b.n_valid = w.n_valid;
+  b.span_count = w.span_count;
+  b.tile_heads = w.tile_heads;
+  return b;
+}
 
 // The key build with the histograms, then the radix passes over (key, position).
 template <class C>
@@ -1240,10 +1209,11 @@ RadixPlan plan_for_call(int64_t V, const CoalesceVariant& var) {
   return plan_for(key_bits(V, var.row_owner != nullptr, var.P, is_split(var)));
 }
 
-// The keys start in keys_b / vals_b and the passes alternate from keys_a, so
-// the sorted keys and positions are in the buffer the last pass wrote.
-void sorted_arrays(const CoalesceWs& ws, const RadixPlan& plan, const uint32_t** skeys, const int32_t** spos) {
-  const bool odd = plan.npass % 2 == 1;
+// The bucket sort leaves its result in keys_a / vals_a.  The radix passes start
+// in keys_b / vals_b and alternate from keys_a, so the sorted keys and positions
+// are in the buffer the last pass wrote.
+void sorted_arrays(const CoalesceWs& ws, const RadixPlan& plan, int T, const uint32_t** skeys, const int32_t** spos) {
+  const bool odd = bucket_sorted(T) || plan.npass % 2 == 1;
   *skeys = odd ? ws.keys_a : ws.keys_b;
   *spos = odd ? ws.vals_a : ws.vals_b;
 }
@@ -1290,23 +1260,19 @@ hipError_t sort_chain(const int32_t* ids, int T, int64_t V, int D, const Coalesc
   }
   // a small batch is sorted and summed by one kernel of the reduction half
   if (!full && small_batch(T, ks)) return hipGetLastError();
-  // 1-3. the key of every token (owner and next-batch lookups once) with the digit
+  if (bucket_sorted(T)) {
+    launch_bucket_sort(ids, T, ks, plan.B, bucket_ws(ws), ws.sort_lb + T, nred, status, stream);
+    return hipGetLastError();
+  }
+  // the key of every token (owner and next-batch lookups once) with the digit
   // histograms of all passes, then the radix passes over (key, position)
   const uint32_t* kin = nullptr;
   const int32_t* vin = nullptr;
-  const bool big = T > kBigTileAbove;
-  if (plan.digit == 9) {
-    if (big)
-      launch_sort<Wide9Big>(ids, T, ks, plan, ws, status, stream, &kin, &vin);
-    else
-      launch_sort<Wide9>(ids, T, ks, plan, ws, status, stream, &kin, &vin);
-  } else {
-    if (big)
-      launch_sort<NarrowBig>(ids, T, ks, plan, ws, status, stream, &kin, &vin);
-    else
-      launch_sort<Narrow>(ids, T, ks, plan, ws, status, stream, &kin, &vin);
-  }
-  // 4. heads per reduction workgroup
+  if (plan.digit == 9)
+    launch_sort<Wide9>(ids, T, ks, plan, ws, status, stream, &kin, &vin);
+  else
+    launch_sort<Narrow>(ids, T, ks, plan, ws, status, stream, &kin, &vin);
+  // heads per reduction workgroup
   hipLaunchKernelGGL(seg_count_kernel, dim3((nred + kWaves - 1) / kWaves), dim3(kThreads), 0, stream, kin, ws.n_valid,
                      ws.tile_heads, nred);
   return hipGetLastError();
@@ -1381,8 +1347,8 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
   const int nred = (T + kRedTile - 1) / kRedTile;
   const uint32_t* kin = nullptr;
   const int32_t* vin = nullptr;
-  sorted_arrays(ws, plan, &kin, &vin);
-  // 5. segments and their sums; 6. ids that cross reduction workgroups
+  sorted_arrays(ws, plan, T, &kin, &vin);
+  // 4. segments and their sums; 5. ids that cross reduction workgroups
   const bool vec4 = (D % 4 == 0) && (reinterpret_cast<uintptr_t>(grad) % (grad_bf16 ? 8 : 16) == 0) &&
                     (reinterpret_cast<uintptr_t>(uniq_grad) % 16 == 0);
   const dim3 cgrid(grid_for(nred, 256), grid_for((D / (vec4 ? 4 : 1) + kWave - 1) / kWave, 8));
@@ -1432,7 +1398,7 @@ hipError_t launch_lookup_request(const int32_t* ids, int T, int64_t V, const int
   const RadixPlan plan = plan_for_call(V, var);
   const uint32_t* kin = nullptr;
   const int32_t* vin = nullptr;
-  sorted_arrays(ws, plan, &kin, &vin);
+  sorted_arrays(ws, plan, T, &kin, &vin);
   const int nred = (T + kRedTile - 1) / kRedTile;
   hipLaunchKernelGGL(request_kernel, dim3(nred), dim3(kRedTile), 0, stream, kin, vin, ws.n_valid, T, ws.tile_heads, ks,
                      ids, req_ids, req_offsets, num_unique, inverse);

@@ -1,9 +1,17 @@
 """The coalesce's paths by batch size, at the edges of their tiles, against the oracle: every kernel
 variant of the small batches (512, 1024 and 2048 tokens) with whole, partial and looped column
-slices, vector and scalar rows, and both gradient types."""
+slices, vector and scalar rows, and both gradient types; the bucket sort's bucket and tile sizes, and
+the first batch past it; the lookup requests and device-side token counts over the same paths."""
+import numpy as np
 import pytest
+import torch
 
+import oracle
+import paper_2110_09132_amd as emb
+import tolerance
+from gpu_helpers import check_coalesce, host, to_dev
 from test_gpu_by_owner import check_by_owner, grads_for, ids_for, owners
+from test_gpu_lookup_request import check_request
 
 pytestmark = pytest.mark.gpu
 
@@ -23,3 +31,82 @@ def test_small_batches_of_wide_rows(T, D):
     V, P = 5000, 8
     ids = ids_for("zipf", T + D, T, V, 1.3)
     check_by_owner(ids, grads_for(T + D, T, D, 0.01), V, owners("range", V, P), P)
+
+
+# ------------------------------------------------------------------ bucket sort
+def sample_tokens(n, T):
+    """The tokens the bucket sort samples (sample_token in bucket_sort.hip)."""
+    i = np.arange(n, dtype=np.uint64)
+    lo, hi = (i * np.uint64(T)) // np.uint64(n), ((i + np.uint64(1)) * np.uint64(T)) // np.uint64(n)
+    m = np.uint64(0xFFFFFFFF)
+    h = (i * np.uint64(0x9E3779B1) + np.uint64(0x7F4A7C15)) & m
+    h ^= h >> np.uint64(15)
+    h = (h * np.uint64(0x85EBCA77)) & m
+    h ^= h >> np.uint64(13)
+    return (lo + ((h * np.maximum(hi - lo, np.uint64(1))) >> np.uint64(32))).astype(np.int64)
+
+
+# distinct ids of the tokens outside the one-key bucket: spread evenly, bunched at the low end (more
+# than 64 in an interval: radix passes), a handful (one radix pass), and over the whole 32-bit key
+LAWS = {"even": (1 << 20, 1 << 20), "bunched": (1 << 20, 300), "few": (1 << 20, 9), "wide": ((1 << 31) - 1, 1 << 31)}
+
+
+@pytest.mark.parametrize("law", sorted(LAWS))
+@pytest.mark.parametrize("m", [1, 511, 513, 1025, 2049, 4096, 4097, 20000])
+def test_bucket_of_any_size(m, law):
+    # every sampled token holds id 5, so the ids above it fall into one bucket of m tokens: each
+    # variant of the bucket's sort, and the one for buckets that do not fit in LDS
+    V, top = LAWS[law]
+    T, D = 30000, 4
+    rng = np.random.default_rng(m)
+    ids = np.full(T, 5, np.int32)
+    free = np.setdiff1d(np.arange(T), sample_tokens(512, T))
+    at = rng.choice(free, m, replace=False)
+    ids[at] = rng.integers(6, min(top, V), m)
+    if law == "bunched":
+        ids[at[0]] = V - 1  # the range is wide all the same
+    G = grads_for(m, T, D, 0.01)
+    if law == "wide":
+        check_coalesce(ids, G, V)
+    else:
+        check_by_owner(ids, G, V, owners("range", V, 4), 4)
+
+
+@pytest.mark.parametrize("T", [2049, 3071, 3073, 131072, 131073, 133121, 262144, 262145, 266241, 655360, 655361])
+@pytest.mark.parametrize("s", [0.0, 1.0, 1.5])
+def test_batch_sizes(T, s):
+    # edges of the sort's tiles and of the three bucket counts, the largest bucket-sorted batch and
+    # the smallest radix-sorted one; even ids, and hot ids with buckets of their own
+    V, P, D = 1 << 18, 5, 4
+    ids = ids_for("uniform" if s == 0.0 else "zipf", T, T, V, s)
+    ids[3::1001] = -1
+    own = owners("mod", V, P)
+    own[7::500] = P  # not an owner
+    check_by_owner(ids, grads_for(T, T, D, 0.01), V, own, P)
+
+
+@pytest.mark.parametrize("T", [1, 63, 700, 1025, 140000, 270000])
+def test_lookup_request_sizes(T):
+    V, P = 40000, 7
+    ids = ids_for("zipf", T, T, V)
+    own = owners("range", V, P)
+    check_request(ids, V, own, P)
+
+
+@pytest.mark.parametrize("count", [0, 1, 3000, 139999])
+def test_device_count_over_all_samples(count):
+    # a device-side token count: the samples come from the tokens that exist
+    T, V, P, D = 140000, 5000, 3, 4
+    ids = ids_for("zipf", 3, T, V)
+    G = grads_for(3, T, D, 0.01)
+    own = owners("mod", V, P)
+    out = emb.receive_merge(to_dev(ids), to_dev(G), to_dev(np.array([count], np.int32)), V, to_dev(own), P)
+    torch.cuda.synchronize()
+    merged_ids, seg, rows, counts, offs, nu = (host(x) for x in out)
+    U = int(nu[0])
+    orc = oracle.coalesce(ids[:count], G[:count], V)
+    pk = oracle.pack_by_owner(orc["uniq_ids"], orc["uniq_grad"], own, P)
+    assert U == orc["U"] and np.array_equal(merged_ids[:U], pk["send_ids"])
+    assert np.array_equal(counts, pk["send_counts"]) and np.array_equal(offs, pk["send_offsets"])
+    idx = np.searchsorted(orc["uniq_ids"], merged_ids[:U])
+    tolerance.assert_grad_close(rows[:U], orc["sum_f64"][idx], orc["absum"][idx])
