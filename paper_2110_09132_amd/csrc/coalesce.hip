@@ -807,9 +807,11 @@ __global__ __launch_bounds__(kCombineThreads) void seg_combine_kernel(const floa
 // memory.  The outputs are those of the multi-kernel path; the fp32 sums of
 // segments that would cross a 32-token chunk there are rounded in another
 // order (a plain sorted-order sum here), within the same bound.
-// What bounds it is latency: about 2 us per sort pass, then one round trip.
+// What bounds it is latency (stamps, 2000 x 1024, Zipf ids): keys 0.8 us, two
+// sort passes 6.5, segments 1.7, the staging 4, the sums 4.2 (a row of 170
+// tokens; 8.0 with clamped reads that waited for each block of eight).
 // Measured per training step of 2000 tokens with rows of 1024 floats: 299 us
-// with one workgroup summing every column (the kernel 276 us), 43 us with
+// with one workgroup summing every column (the kernel 276 us), 39 us with
 // a workgroup per slice; 512 tokens of 64 floats, the kernel: 12.9 -> 10.2 us.
 constexpr int kSmallMax = 2048;
 constexpr int kSmallGroupsMax = 2 * 1024;  // owner groups, times two with the split
@@ -956,14 +958,45 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
     __syncthreads();
     for (int u = grp; u < U; u += NT / L) {
       const int S = sstart[u], E = sstart[u + 1];
+      const Acc* row = stage + S * L + cl;
+      const int len = E - S;
       Acc acc = Acc{};
-      for (int e = S; e < E; e += kSmallUnroll) {
-        Acc v[kSmallUnroll];
+      // a long segment is a chain of additions: the next eight rows are read while
+      // the current eight are added (two buffers in turn, no clamps or branches)
+      const int blocks = len / kSmallUnroll;
+      Acc va[kSmallUnroll], vb[kSmallUnroll];
+      auto read = [&](Acc(&v)[kSmallUnroll], int i) {
 #pragma unroll
-        for (int k = 0; k < kSmallUnroll; ++k) v[k] = stage[min(e + k, E - 1) * L + cl];
+        for (int k = 0; k < kSmallUnroll; ++k) v[k] = row[(i * kSmallUnroll + k) * L];
+      };
+      auto add = [&](const Acc(&v)[kSmallUnroll]) {
 #pragma unroll
-        for (int k = 0; k < kSmallUnroll; ++k)
-          if (e + k < E) acc += v[k];
+        for (int k = 0; k < kSmallUnroll; ++k) acc += v[k];
+      };
+      if (blocks > 0) {
+        read(va, 0);
+        int i = 1;
+        for (; i + 2 <= blocks; i += 2) {
+          read(vb, i);
+          add(va);
+          read(va, i + 1);
+          add(vb);
+        }
+        if (i < blocks) {
+          read(vb, i);
+          add(va);
+          add(vb);
+        } else {
+          add(va);
+        }
+      }
+      const int done = blocks * kSmallUnroll;
+      if (done < len) {
+#pragma unroll
+        for (int k = 0; k < kSmallUnroll - 1; ++k) va[k] = row[min(done + k, len - 1) * L];
+#pragma unroll
+        for (int k = 0; k < kSmallUnroll - 1; ++k)
+          if (done + k < len) acc += va[k];
       }
       if (c < Dv) out[static_cast<size_t>(u) * Dv + c] = acc;
     }
