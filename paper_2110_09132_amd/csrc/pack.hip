@@ -10,6 +10,12 @@
 //     slot of every row; ids are written there, the slot is kept for step 3;
 //     tile 0 writes send_counts / send_offsets,
 //  3. the rows are copied to their slots (contiguous row reads and writes).
+// With few tiles and owners (all histograms a few words per thread) 2 and 3 are
+// one kernel (pack_place): a workgroup takes a few consecutive rows of a tile,
+// issues their loads, finds their slots meanwhile, and stores them there.  For
+// small packs the launches and the round trips between them are most of the
+// time: 7100 rows of 2 KB, 4 owners 19.5 -> 14.0 us a call, 200 of 256 bytes
+// 18.9 -> 11.7, 63500 of 1 KB, 16 owners 37.7 -> 33.4.
 #include "common.h"
 #include "launch.h"
 
@@ -22,6 +28,13 @@ constexpr int kTile = kThreads * kItems;  // rows per tile
 constexpr int kMaxOwners = 1024;
 constexpr int kBinsMax = kMaxOwners + 1;
 constexpr int kRowsInFlight = 8;
+// Slots and copy are one kernel up to these sizes: histogram words of all tiles,
+// bins (its LDS, and so its workgroups per CU, grow with them), and tiles.  With
+// 1025 bins it ran three workgroups per CU: 63500 rows of 1 KB, 16 owners, 38.9
+// us against 33.4; at 391 tiles 53.8 us against 52.2 with separate kernels.
+constexpr int kPlaceHistWords = 8192;
+constexpr int kPlaceBins = 257;
+constexpr int kPlaceTiles = 256;
 
 __device__ __forceinline__ int clamp_rows(const int32_t* num_unique, int cap) {
   const int u = num_unique[0];
@@ -165,6 +178,78 @@ __global__ __launch_bounds__(kThreads) void pack_rows_kernel(const VecT* __restr
   }
 }
 
+// Steps 2 and 3 for `rows` consecutive rows of a tile (a power of two, at most
+// kThreads): their source is one contiguous run of rows * Dv vectors, which the
+// threads walk in order whatever the width.
+template <typename VecT>
+__global__ __launch_bounds__(kThreads) void pack_place_kernel(
+    const int32_t* __restrict__ uniq_ids, const VecT* __restrict__ uniq_grad, const int32_t* __restrict__ num_unique,
+    int cap, const uint16_t* __restrict__ digit_of, int P, int owner_bits, const uint32_t* __restrict__ tile_hist,
+    int ntiles, int Dv, int rows, int32_t* __restrict__ send_ids, VecT* __restrict__ send_rows,
+    int32_t* __restrict__ send_counts, int32_t* __restrict__ send_offsets) {
+  __shared__ uint32_t cnt[(kThreads / kWave) * kPlaceBins];
+  __shared__ uint32_t dstart[kPlaceBins], colall[kPlaceBins], gbase[kPlaceBins];
+  __shared__ uint32_t red_all[kPlaceBins], red_bef[kPlaceBins];
+  __shared__ uint32_t before[kPlaceBins];  // rows of each owner in the tile before this workgroup's
+  __shared__ uint32_t wsum[kThreads / kWave];
+  __shared__ int32_t slot[kThreads];
+  const int bins = P + 1;
+  const int tid = static_cast<int>(threadIdx.x);
+  const int r0 = static_cast<int>(blockIdx.x) * rows;
+  const int U = clamp_rows(num_unique, cap);
+  if (r0 >= U && blockIdx.x != 0) return;  // (the first workgroup writes the counts in any case)
+  const int n = max(min(rows, U - r0), 0);
+  const int tile = r0 / kTile;
+  const int units = n * Dv;
+  const VecT* src = uniq_grad + static_cast<size_t>(r0) * Dv;
+  // the rows' loads first: nothing below depends on them
+  VecT v[kRowsInFlight];
+#pragma unroll
+  for (int k = 0; k < kRowsInFlight; ++k) v[k] = units > 0 ? src[min(tid + k * kThreads, units - 1)] : VecT{};
+  const int row = min(r0 + tid, max(U - 1, 0));
+  const bool valid[1] = {tid < n};
+  const int32_t id = uniq_ids[row];
+  const uint32_t mine = min(static_cast<uint32_t>(digit_of[row]), static_cast<uint32_t>(P));
+  uint32_t dig[1] = {valid[0] ? mine : 0u}, lpos[1];
+  for (int d = tid; d < bins; d += kThreads) before[d] = 0;
+  __syncthreads();
+  for (int k = tile * kTile + tid; k < r0; k += kThreads)
+    atomicAdd(&before[min(static_cast<uint32_t>(digit_of[k]), static_cast<uint32_t>(P))], 1u);
+  const uint32_t total =
+      tile_global_bases<kThreads>(tile_hist, ntiles, tile, bins, colall, gbase, red_all, red_bef, wsum);
+  tile_stable_rank<kThreads, 1>(dig, valid, bins, owner_bits, cnt, dstart, wsum, lpos);
+  int32_t dest = -1;
+  if (valid[0] && dig[0] != static_cast<uint32_t>(P)) {
+    const uint32_t d = dig[0];
+    dest = static_cast<int32_t>(gbase[d] + before[d] + (lpos[0] - dstart[d]));
+    if (dest >= cap) dest = -1;  // (only with a workspace overwritten meanwhile)
+    if (dest >= 0) send_ids[dest] = id;
+  }
+  slot[tid] = dest;
+  if (blockIdx.x == 0) {
+    for (int p = tid; p < P; p += kThreads) {
+      send_counts[p] = static_cast<int32_t>(colall[p]);
+      send_offsets[p] = static_cast<int32_t>(gbase[p]);  // the first rows: nothing before them
+    }
+    if (tid == 0) send_offsets[P] = static_cast<int32_t>(total - colall[P]);
+  }
+  __syncthreads();
+  for (int i0 = 0; i0 < units; i0 += kRowsInFlight * kThreads) {
+    if (i0 > 0) {
+#pragma unroll
+      for (int k = 0; k < kRowsInFlight; ++k) v[k] = src[min(i0 + tid + k * kThreads, units - 1)];
+    }
+#pragma unroll
+    for (int k = 0; k < kRowsInFlight; ++k) {
+      const int i = i0 + tid + k * kThreads;
+      if (i >= units) continue;
+      const int r = i / Dv;
+      const int to = slot[r];
+      if (to >= 0) send_rows[static_cast<size_t>(to) * Dv + (i - r * Dv)] = v[k];
+    }
+  }
+}
+
 struct PackWs {
   uint32_t* tile_hist;
   int32_t* slot_of;
@@ -208,12 +293,30 @@ hipError_t launch_pack(const int32_t* uniq_ids, const float* uniq_grad, const in
   while ((1 << owner_bits) <= P) ++owner_bits;  // digits 0..P
   hipLaunchKernelGGL(pack_hist_kernel, dim3(ntiles), dim3(kThreads), 0, stream, uniq_ids, num_unique, cap_rows,
                      row_owner, V, P, ws.tile_hist, ws.digit_of, status);
-  hipLaunchKernelGGL(pack_scatter_kernel, dim3(ntiles), dim3(kThreads), 0, stream, uniq_ids, num_unique, cap_rows,
-                     ws.digit_of, P, owner_bits, ws.tile_hist, ntiles, send_ids, ws.slot_of, send_counts,
-                     send_offsets);
   const bool vec4 = (D % 4 == 0) && (reinterpret_cast<uintptr_t>(uniq_grad) % 16 == 0) &&
                     (reinterpret_cast<uintptr_t>(send_rows) % 16 == 0);
   const int Dv = vec4 ? D / 4 : D;
+  // every workgroup of the one-kernel form sums all tiles' histograms: worth a
+  // launch and the slots' round trip while that is a few loads per thread
+  if (P + 1 <= kPlaceBins && ntiles <= kPlaceTiles &&
+      static_cast<long long>(ntiles) * (P + 1) <= kPlaceHistWords) {
+    int rows = kThreads;  // about kRowsInFlight vectors per thread
+    while (rows > 1 && static_cast<long long>(rows) * Dv > kRowsInFlight * kThreads) rows /= 2;
+    const unsigned groups = static_cast<unsigned>((static_cast<long long>(cap_rows) + rows - 1) / rows);
+    if (vec4)
+      hipLaunchKernelGGL(pack_place_kernel<float4>, dim3(groups), dim3(kThreads), 0, stream, uniq_ids,
+                         reinterpret_cast<const float4*>(uniq_grad), num_unique, cap_rows, ws.digit_of, P, owner_bits,
+                         ws.tile_hist, ntiles, Dv, rows, send_ids, reinterpret_cast<float4*>(send_rows), send_counts,
+                         send_offsets);
+    else
+      hipLaunchKernelGGL(pack_place_kernel<float>, dim3(groups), dim3(kThreads), 0, stream, uniq_ids, uniq_grad,
+                         num_unique, cap_rows, ws.digit_of, P, owner_bits, ws.tile_hist, ntiles, Dv, rows, send_ids,
+                         send_rows, send_counts, send_offsets);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(pack_scatter_kernel, dim3(ntiles), dim3(kThreads), 0, stream, uniq_ids, num_unique, cap_rows,
+                     ws.digit_of, P, owner_bits, ws.tile_hist, ntiles, send_ids, ws.slot_of, send_counts,
+                     send_offsets);
   const RowLanes rl = row_lanes_for(Dv);
   const long long rows_per_block = static_cast<long long>(rl.rows_per_wave()) * kRowsInFlight * (kThreads / kWave);
   const unsigned grid = grid_for((cap_rows + rows_per_block - 1) / rows_per_block, kMaxBlocks);

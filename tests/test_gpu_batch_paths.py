@@ -110,3 +110,28 @@ def test_device_count_over_all_samples(count):
     assert np.array_equal(counts, pk["send_counts"]) and np.array_equal(offs, pk["send_offsets"])
     idx = np.searchsorted(orc["uniq_ids"], merged_ids[:U])
     tolerance.assert_grad_close(rows[:U], orc["sum_f64"][idx], orc["absum"][idx])
+
+
+# ------------------------------------------------------------------------- pack
+@pytest.mark.parametrize("T,D,P", [(700, 3, 2), (1024, 4, 1), (1025, 2052, 7), (3000, 260, 3), (5000, 9000, 2),
+                                   (4096, 16, 1024), (9000, 8, 256), (9000, 8, 257), (40000, 12, 203), (40000, 12, 204)])
+def test_pack_places(T, D, P):
+    # rows per workgroup from one to all of its threads, both sides of the histogram limit, more
+    # vectors than one round of loads, rows without an owner
+    V = 60000
+    ids = ids_for("uniform", T + P, T, V)
+    own = owners("rand", V, P, seed=T)
+    own[::11] = -1
+    out = emb.grad_coalesce(to_dev(ids), to_dev(grads_for(T, T, D, 0.01)), V)
+    torch.cuda.synchronize()
+    U = int(out[3].item())
+    uid, ug = host(out[0][:U]), host(out[2][:U])
+    want = oracle.pack_by_owner(uid, ug, own, P)
+    st = emb.new_status()
+    send_ids, rows, counts, offs = emb.pack_by_owner(out[0], out[2], out[3], to_dev(own), P, dev_status=st)
+    torch.cuda.synchronize()
+    n = int(want["send_offsets"][P])
+    assert np.array_equal(host(counts), want["send_counts"]) and np.array_equal(host(offs), want["send_offsets"])
+    assert np.array_equal(host(send_ids[:n]), want["send_ids"])
+    assert np.array_equal(host(rows[:n]).view(np.uint32), want["send_rows"].view(np.uint32))
+    assert int(st.item()) == emb.EMB_DEV_OWNER_OUT_OF_RANGE
