@@ -170,6 +170,7 @@ __global__ __launch_bounds__(C::kThreads) void bucket_split_kernel(const int32_t
   const int lane = static_cast<int>(lane_id());
   const int tile = static_cast<int>(blockIdx.x);
   const int Tc = ks.count_dev != nullptr ? min(max(*ks.count_dev, 0), T) : T;  // tokens that exist
+  extern __shared__ uint32_t next_bits[];  // a bit per row that occurs in the next batch (ks.next_ids)
   // this thread's tokens, element (wave, round, lane) as the ranking walks them, and its samples
   int32_t id[kAll];
   int t[kAll];
@@ -188,6 +189,29 @@ __global__ __launch_bounds__(C::kThreads) void bucket_split_kernel(const int32_t
     own[r] = 0;
     if (ks.row_owner != nullptr) own[r] = static_cast<uint32_t>(ks.row_owner[take[r] ? id[r] : 0]);
   }
+  if (ks.next_ids != nullptr) {
+    constexpr int kBatch = 8;  // next ids in flight per thread
+    const int words = static_cast<int>((ks.V + 31) / 32);
+    for (int i = tid; i < words; i += NT) next_bits[i] = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < ks.T_next; i0 += kBatch * NT) {
+      int32_t nx[kBatch];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) nx[k] = ks.next_ids[min(i0 + k * NT + tid, ks.T_next - 1)];
+      // a look at all their words first: repeated ids (hot rows) then do not
+      // queue on one word's atomic (past the end: the last id again)
+      uint32_t seen[kBatch];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) seen[k] = next_bits[min(static_cast<uint32_t>(nx[k]), ks.V - 1) / 32];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const uint32_t u = static_cast<uint32_t>(nx[k]);  // V < 2^31: a negative id is past every row
+        const uint32_t bit = 1u << (u % 32);
+        if (u < ks.V && (seen[k] & bit) == 0) atomicOr(&next_bits[u / 32], bit);
+      }
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int r = 0; r < kAll; ++r) {
     const bool exists = t[r] < Tc;
@@ -196,7 +220,12 @@ __global__ __launch_bounds__(C::kThreads) void bucket_split_kernel(const int32_t
     bad_owner |= r < kItems && exists && take[r] && !ownok;
     take[r] = exists && take[r] && ownok;
     key[r] = (own[r] << ks.ib) | static_cast<uint32_t>(id[r]);
-    if (ks.next_tab != nullptr && take[r] && !in_next(static_cast<uint32_t>(id[r]), ks)) key[r] |= 1u << ks.cls_shift;
+    if (ks.next_ids != nullptr) {
+      const uint32_t u = take[r] ? static_cast<uint32_t>(id[r]) : 0u;
+      if (take[r] && ((next_bits[u / 32] >> (u % 32)) & 1u) == 0) key[r] |= 1u << ks.cls_shift;
+    } else if (ks.next_tab != nullptr && take[r] && !in_next(static_cast<uint32_t>(id[r]), ks)) {
+      key[r] |= 1u << ks.cls_shift;
+    }
   }
   if (__any(bad_id) && lane == 0) raise_flag(status, EMB_DEV_ID_OUT_OF_RANGE);
   if (__any(bad_owner) && lane == 0) raise_flag(status, EMB_DEV_OWNER_OUT_OF_RANGE);
@@ -588,6 +617,7 @@ __global__ __launch_bounds__(kNT) void bucket_sort_kernel(int T, int ntiles, int
 
 void launch_bucket_sort(const int32_t* ids, int T, const KeySpec& ks, int key_bits, BucketWs ws, uint32_t* words,
                         int nred, int32_t* status, hipStream_t stream) {
+  const size_t next_lds = ks.next_ids != nullptr ? (ks.V + 31) / 32 * sizeof(uint32_t) : 0;
 #define EMB_BUCKET(C)                                                                                               \
   do {                                                                                                              \
     const int ntiles = (T + C::kTile - 1) / C::kTile;                                                               \
@@ -595,8 +625,8 @@ void launch_bucket_sort(const int32_t* ids, int T, const KeySpec& ks, int key_bi
     ws.heavy = words + C::kBuckets;                                                                                 \
     ws.starts = reinterpret_cast<uint16_t*>(words + C::kBuckets + C::kHeavyWords + 1);                              \
     ws.heavy_dst = reinterpret_cast<int32_t*>(words + C::kBuckets + C::kHeavyWords + 1 + ntiles * (C::kRow / 2));   \
-    hipLaunchKernelGGL(bucket_split_kernel<C>, dim3(ntiles), dim3(C::kThreads), 0, stream, ids, T, ks, ws, nred,    \
-                       status);                                                                                     \
+    hipLaunchKernelGGL(bucket_split_kernel<C>, dim3(ntiles), dim3(C::kThreads), next_lds, stream, ids, T, ks, ws,   \
+                       nred, status);                                                                               \
     hipLaunchKernelGGL(bucket_sort_kernel<C>, dim3(C::kBuckets + (C::kCopyKernel ? 0 : ntiles)), dim3(kNT), 0,      \
                        stream, T, ntiles, key_bits, ws);                                                            \
     if (C::kCopyKernel)                                                                                             \

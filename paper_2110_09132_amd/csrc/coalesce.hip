@@ -255,6 +255,8 @@ KeySpec key_spec(int64_t V, const int32_t* row_owner, int P, bool split) {
   ks.next_tab = nullptr;
   ks.next_bytemap = false;
   ks.tab_shift = 32;
+  ks.next_ids = nullptr;
+  ks.T_next = 0;
   ks.G = (own && split) ? 2 * P : ks.P;
   ks.count_dev = nullptr;
   return ks;
@@ -824,6 +826,36 @@ constexpr int kXcds = 8;
 // Vectors of one row's slice: what the staging area holds for `rows` rows.
 constexpr int small_slice(int rows, int vec) { return kSmallStage / (rows * vec * static_cast<int>(sizeof(float))); }
 
+// A set of ids in LDS: open addressing, slot value id + 1, 0 = empty, at most a
+// quarter full.
+constexpr int kSmallSetLog2 = 13;
+constexpr int kSmallSetSlots = 1 << kSmallSetLog2;
+// Next ids that the small-batch kernel takes itself, every workgroup all of
+// them (512 tokens and next ids: 13.8 -> 9.9 us a call; 2000: 21.6 -> 20.1; 4096
+// next ids 21.6 -> 25, so those keep the set in memory).
+constexpr int kSmallNextIds = kSmallSetSlots / 4;
+static_assert(kSmallSetSlots * sizeof(uint32_t) <= kSmallStage, "the set fits the staging area");
+
+__device__ __forceinline__ void lds_set_add(uint32_t* set, uint32_t id) {
+  uint32_t slot = tab_slot(id, 32 - kSmallSetLog2);
+  for (int probe = 0; probe < kSmallSetSlots; ++probe) {
+    uint32_t v = set[slot];  // a plain look first: repeated ids do not queue on an atomic
+    if (v == 0u) v = atomicCAS(&set[slot], 0u, id + 1u);
+    if (v == 0u || v == id + 1u) return;
+    slot = (slot + 1) & (kSmallSetSlots - 1);
+  }
+}
+__device__ __forceinline__ bool lds_set_has(const uint32_t* set, uint32_t id) {
+  uint32_t slot = tab_slot(id, 32 - kSmallSetLog2);
+  for (int probe = 0; probe < kSmallSetSlots; ++probe) {
+    const uint32_t v = set[slot];
+    if (v == id + 1u) return true;
+    if (v == 0u) return false;
+    slot = (slot + 1) & (kSmallSetSlots - 1);
+  }
+  return false;
+}
+
 template <bool BF16, int VEC, int NT, int IT>
 __global__ __launch_bounds__(NT) void small_coalesce_kernel(
     const int32_t* __restrict__ ids, int T, KeySpec ks, int npass, int bits, const void* __restrict__ grad, int D,
@@ -861,6 +893,16 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
     pos[r] = w * IT * kWave + r * kWave + lane;
     id[r] = ids[min(pos[r], T - 1)];
   }
+  uint32_t* set = reinterpret_cast<uint32_t*>(stage_s);
+  if (ks.next_ids != nullptr) {  // the next batch's ids, in the staging area for now
+    for (int i = threadIdx.x; i < kSmallSetSlots; i += NT) set[i] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < ks.T_next; i += NT) {
+      const int32_t nx = ks.next_ids[i];
+      if (nx >= 0 && static_cast<uint32_t>(nx) < ks.V) lds_set_add(set, static_cast<uint32_t>(nx));
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int r = 0; r < IT; ++r) {
     const bool inb = pos[r] < Tc;
@@ -872,8 +914,13 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
     bad_id |= inb && !idok;
     bad_owner |= inb && idok && !ownok;
     key[r] = (own << ks.ib) | static_cast<uint32_t>(idok ? id[r] : 0);
-    if (ks.next_tab != nullptr && valid[r] && !in_next(static_cast<uint32_t>(id[r]), ks)) key[r] |= 1u << ks.cls_shift;
+    if (ks.next_ids != nullptr) {
+      if (valid[r] && !lds_set_has(set, static_cast<uint32_t>(id[r]))) key[r] |= 1u << ks.cls_shift;
+    } else if (ks.next_tab != nullptr && valid[r] && !in_next(static_cast<uint32_t>(id[r]), ks)) {
+      key[r] |= 1u << ks.cls_shift;
+    }
   }
+  if (ks.next_ids != nullptr) __syncthreads();  // the sort's counters overwrite the set
   if (meta && __any(bad_id) && lane == 0) raise_flag(status, EMB_DEV_ID_OUT_OF_RANGE);
   if (meta && __any(bad_owner) && lane == 0) raise_flag(status, EMB_DEV_OWNER_OUT_OF_RANGE);
   // 2. LSD radix passes in LDS; the first ranks only the tokens that take part
@@ -1270,6 +1317,13 @@ unsigned small_blocks(int Dv, int L) {
 // Batches that one launch coalesces (their groups fit its LDS table).
 bool small_batch(int T, const KeySpec& ks) { return T <= kSmallMax && ks.G <= kSmallGroupsMax; }
 
+// The split's set of next ids is built in LDS by the kernel that forms the keys
+// (no launches of its own).
+bool next_in_lds(int T, int64_t V, const KeySpec& ks, const CoalesceVariant& var) {
+  if (!is_split(var) || var.T_next == 0) return false;  // (an empty next batch: the empty set in memory)
+  return small_batch(T, ks) ? var.T_next <= kSmallNextIds : bucket_next_in_lds(V, T, var.T_next);
+}
+
 // full: the radix passes and head counts even for a small batch (the lookup
 // requests read the sorted keys).
 hipError_t sort_chain(const int32_t* ids, int T, int64_t V, int D, const CoalesceVariant& var, void* workspace,
@@ -1281,7 +1335,10 @@ hipError_t sort_chain(const int32_t* ids, int T, int64_t V, int D, const Coalesc
   const RadixPlan plan = plan_for_call(V, var);
   const int nred = (T + kRedTile - 1) / kRedTile;
   // 0. the next batch's ids into a set (vertical split)
-  if (is_split(var)) {
+  if (next_in_lds(T, V, ks, var)) {
+    ks.next_ids = var.next_ids;
+    ks.T_next = var.T_next;
+  } else if (is_split(var)) {
     hipLaunchKernelGGL(tab_clear_kernel, dim3(grid_for((ws.tab_words + kThreads - 1) / kThreads, 1024)),
                        dim3(kThreads), 0, stream, ws.next_tab, ws.tab_words);
     if (var.T_next > 0)
@@ -1334,7 +1391,10 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
     const CoalesceWs wsn = carve(workspace, T, D, is_split(var) ? var.T_next : -1, V);
     KeySpec kss = ks;
     kss.count_dev = var.count_dev;
-    if (is_split(var)) {
+    if (next_in_lds(T, V, ks, var)) {
+      kss.next_ids = var.next_ids;
+      kss.T_next = var.T_next;
+    } else if (is_split(var)) {
       kss.next_tab = wsn.next_tab;
       kss.next_bytemap = wsn.tab_bytemap;
       kss.tab_shift = wsn.tab_shift;

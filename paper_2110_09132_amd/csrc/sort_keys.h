@@ -22,6 +22,8 @@ struct KeySpec {
                              // row of [0, V) (next_bytemap), else a hash set of 2^(32 - tab_shift) slots
   bool next_bytemap;
   int tab_shift;
+  const int32_t* next_ids;   // if given (and next_tab is not): the kernel builds the set in LDS from
+  int T_next;                // these ids
   int G;                     // groups of the output: owners, times 2 with the split
   const int32_t* count_dev;  // if given: only the first *count_dev tokens take part
 };
@@ -63,6 +65,17 @@ struct BucketWs {
   uint16_t* starts;                 // per tile: where each bucket starts in it, and its token count
   int32_t* heavy_dst;               // per tile: where its tokens of each one-key bucket go
 };
+// The vertical split's set of next ids is built in LDS by each workgroup of the
+// bucket sort's first kernel (a bit per row), up to these sizes: two launches
+// (clear and insert, 6.5 us with their gaps) against reading the ids once per
+// tile, which costs as much at 20000 ids (split calls, 4096 tokens and next ids:
+// 30.5 -> 27.1 us; 16384: 30.5 -> 28.5 uniform, 31.1 -> 29.4 Zipf; 25000: 29.9 ->
+// 31.3 and 31.2 -> 31.8).
+constexpr int64_t kLdsNextRows = 1 << 18;
+constexpr int kLdsNextIds = 1 << 14;
+inline bool bucket_next_in_lds(int64_t V, int T, int T_next) {
+  return T <= 1 << 17 && V <= kLdsNextRows && T_next <= kLdsNextIds;
+}
 constexpr int kBucketMaxTokens = 5 << 17;  // the most tokens the bucket sort takes
 // Sorts T (1 .. kBucketMaxTokens) tokens by (key, position); key_bits: bits of
 // the keys; words: 3/2 words per token (T rounded up to 1024) less T words.

@@ -10,7 +10,7 @@ import oracle
 import paper_2110_09132_amd as emb
 import tolerance
 from gpu_helpers import check_coalesce, host, to_dev
-from test_gpu_by_owner import check_by_owner, grads_for, ids_for, owners
+from test_gpu_by_owner import check_by_owner, check_split, grads_for, ids_for, owners
 from test_gpu_lookup_request import check_request
 
 pytestmark = pytest.mark.gpu
@@ -135,3 +135,18 @@ def test_pack_places(T, D, P):
     assert np.array_equal(host(send_ids[:n]), want["send_ids"])
     assert np.array_equal(host(rows[:n]).view(np.uint32), want["send_rows"].view(np.uint32))
     assert int(st.item()) == emb.EMB_DEV_OWNER_OUT_OF_RANGE
+
+
+# ------------------------------------------------------------------------ split
+@pytest.mark.parametrize("T,T_next,V", [
+    (300, 1, 1000), (1000, 2048, 900000), (2048, 2048, 1 << 25), (2000, 2049, 5000),  # small batches
+    (2049, 1, 1 << 18), (5000, 16384, 1 << 18), (5000, 16385, 1 << 18), (5000, 700, (1 << 18) + 1), (3000, 8191, 33),
+    (131072, 9000, 40000), (131073, 9000, 40000)])
+@pytest.mark.parametrize("law", ["zipf", "uniform"])
+def test_split_next_sets(T, T_next, V, law):
+    # the next batch's ids as a set in LDS (a hash set for small batches, a bit per row for the bucket
+    # sort) and past its limits in memory; some next ids are not rows
+    ids, nxt = ids_for(law, T, T, V), ids_for(law, T_next + 1, T_next, V)
+    nxt[5::17] = -1
+    nxt[6::17] = V
+    check_split(ids, nxt, grads_for(T, T, 4, 0.01), V, owners("mod", V, 3), 3)
