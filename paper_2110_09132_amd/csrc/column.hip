@@ -49,6 +49,13 @@ __device__ __forceinline__ int col_owner(int c, int Dv, int P) {
   return p;
 }
 
+// kPack: every owner gets all R rows.  Written by the first workgroup (a launch
+// of its own for P words cost the pack 2.6 us of 18).
+__device__ __forceinline__ void write_counts(int32_t* send_counts, int R, int P) {
+  if (send_counts == nullptr || blockIdx.x != 0) return;
+  for (int p = threadIdx.x; p < P; p += kThreads) send_counts[p] = R;
+}
+
 // Rows handled: kPack R = *count clamped to [0, cap] (cap if count is null);
 // kGather R = cap = T; kAssemble R = cap.  src_cap: capacity of the source
 // blocks (kGather: V, kAssemble: the blocks' C); dst_cap: capacity of the
@@ -58,13 +65,14 @@ __global__ __launch_bounds__(kThreads) void column_kernel(const VecT* __restrict
                                                           const int32_t* __restrict__ ids,
                                                           const int32_t* __restrict__ count, int cap,
                                                           int64_t src_cap, int64_t dst_cap, int64_t row0, int Dv,
-                                                          int P, int log2L, int32_t* status) {
+                                                          int P, int log2L, int32_t* send_counts, int32_t* status) {
   const int L = 1 << log2L;
   const int rpw = kWave >> log2L;
   const int lane = static_cast<int>(lane_id());
   const int sub = lane >> log2L;
   const int cl = lane & (L - 1);
   const int R = (kMode == kPack && count != nullptr) ? min(max(*count, 0), cap) : cap;
+  if (kMode == kPack) write_counts(send_counts, R, P);
   if (R == 0) return;
   const int64_t group_rows = static_cast<int64_t>(rpw) * kRowsInFlight;
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * (kThreads / kWave);
@@ -128,6 +136,11 @@ __global__ __launch_bounds__(kThreads) void column_kernel(const VecT* __restrict
 // the rows of a tile start in different banks.  Threads issue kUnroll loads
 // before they store.
 constexpr int kTileUnits = 1024;  // units per tile (16 KB of float4)
+// The pack of float4 takes half of that: more, smaller workgroups, since each
+// waits for its loads before its first store (12288 rows of 4 KB, 8 owners: 25.9
+// -> 22.7 us; 49152 of 1 KB, 16 owners: 24.5 -> 23.5; single floats, whose
+// runs per owner are short, were slower so: 10.8 -> 13.4 at 128 floats, 12 owners).
+constexpr int kPackUnits = 512;
 constexpr int kUnroll = 4;
 constexpr int kLdsPad = 1;
 
@@ -136,11 +149,13 @@ __global__ __launch_bounds__(kThreads) void column_tile_kernel(const VecT* __res
                                                                const int32_t* __restrict__ ids,
                                                                const int32_t* __restrict__ count, int cap,
                                                                int64_t src_cap, int64_t dst_cap, int64_t row0,
-                                                               int Dv, int P, int TR, int32_t* status) {
+                                                               int Dv, int P, int TR, int32_t* send_counts,
+                                                               int32_t* status) {
   extern __shared__ __align__(16) unsigned char column_lds[];
   VecT* tile = reinterpret_cast<VecT*>(column_lds);
   const int ld = Dv + kLdsPad;
   const int R = (kMode == kPack && count != nullptr) ? min(max(*count, 0), cap) : cap;
+  if (kMode == kPack) write_counts(send_counts, R, P);
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * TR;
   if (r0 >= R) return;
   const int n = static_cast<int>(min(static_cast<int64_t>(TR), R - r0));
@@ -223,16 +238,14 @@ __global__ __launch_bounds__(kThreads) void column_tile_kernel(const VecT* __res
   }
 }
 
-__global__ void column_counts_kernel(const int32_t* __restrict__ count, int cap, int P,
-                                     int32_t* __restrict__ send_counts) {
-  const int R = count != nullptr ? min(max(*count, 0), cap) : cap;
-  for (int p = threadIdx.x; p < P; p += blockDim.x) send_counts[p] = R;
+__global__ void empty_counts_kernel(int P, int32_t* __restrict__ send_counts) {
+  for (int p = threadIdx.x; p < P; p += blockDim.x) send_counts[p] = 0;
 }
 
 template <int kMode>
 hipError_t launch_column(const float* src, float* dst, const int32_t* ids, const int32_t* count, int cap,
-                         int64_t src_cap, int64_t dst_cap, int64_t row0, int D, int P, int32_t* status,
-                         hipStream_t stream) {
+                         int64_t src_cap, int64_t dst_cap, int64_t row0, int D, int P, int32_t* send_counts,
+                         int32_t* status, hipStream_t stream) {
   if (cap == 0) return hipSuccess;
   const auto al16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
   const bool vec4 = D % (4 * P) == 0 && al16(src) && al16(dst);
@@ -243,7 +256,7 @@ hipError_t launch_column(const float* src, float* dst, const int32_t* ids, const
   // tiles of up to kTileUnits units (at least one row); rows too wide for a
   // 32 KB tile take the row-per-lanes kernel
   const size_t unit = vec4 ? sizeof(float4) : sizeof(float);
-  const int TR = max(1, kTileUnits / Dv);
+  const int TR = max(1, (kMode == kPack && vec4 ? kPackUnits : kTileUnits) / Dv);
   const size_t lds = static_cast<size_t>(TR) * (Dv + kLdsPad) * unit;
   if (lds <= 32768) {
     const unsigned tiles = static_cast<unsigned>((static_cast<long long>(cap) + TR - 1) / TR);
@@ -251,19 +264,19 @@ hipError_t launch_column(const float* src, float* dst, const int32_t* ids, const
     if (vec4)
       hipLaunchKernelGGL((column_tile_kernel<float4, kMode>), dim3(tiles), dim3(kThreads), shm, stream,
                          reinterpret_cast<const float4*>(src), reinterpret_cast<float4*>(dst), ids, count, cap,
-                         src_cap, dst_cap, row0, Dv, P, TR, status);
+                         src_cap, dst_cap, row0, Dv, P, TR, send_counts, status);
     else
       hipLaunchKernelGGL((column_tile_kernel<float, kMode>), dim3(tiles), dim3(kThreads), shm, stream, src, dst, ids,
-                         count, cap, src_cap, dst_cap, row0, Dv, P, TR, status);
+                         count, cap, src_cap, dst_cap, row0, Dv, P, TR, send_counts, status);
     return hipGetLastError();
   }
   if (vec4)
     hipLaunchKernelGGL((column_kernel<float4, kMode>), dim3(grid), dim3(kThreads), 0, stream,
                        reinterpret_cast<const float4*>(src), reinterpret_cast<float4*>(dst), ids, count, cap,
-                       src_cap, dst_cap, row0, Dv, P, rl.log2_lanes, status);
+                       src_cap, dst_cap, row0, Dv, P, rl.log2_lanes, send_counts, status);
   else
     hipLaunchKernelGGL((column_kernel<float, kMode>), dim3(grid), dim3(kThreads), 0, stream, src, dst, ids, count,
-                       cap, src_cap, dst_cap, row0, Dv, P, rl.log2_lanes, status);
+                       cap, src_cap, dst_cap, row0, Dv, P, rl.log2_lanes, send_counts, status);
   return hipGetLastError();
 }
 
@@ -271,19 +284,21 @@ hipError_t launch_column(const float* src, float* dst, const int32_t* ids, const
 
 hipError_t launch_column_pack(const float* rows, const int32_t* num_rows, int cap, int D, int P, float* blocks,
                               int32_t* send_counts, hipStream_t stream) {
-  if (send_counts != nullptr)
-    hipLaunchKernelGGL(column_counts_kernel, dim3(1), dim3(kThreads), 0, stream, num_rows, cap, P, send_counts);
-  return launch_column<kPack>(rows, blocks, nullptr, num_rows, cap, 0, cap, 0, D, P, nullptr, stream);
+  if (cap == 0 && send_counts != nullptr) {
+    hipLaunchKernelGGL(empty_counts_kernel, dim3(1), dim3(kThreads), 0, stream, P, send_counts);
+    return hipGetLastError();
+  }
+  return launch_column<kPack>(rows, blocks, nullptr, num_rows, cap, 0, cap, 0, D, P, send_counts, nullptr, stream);
 }
 
 hipError_t launch_column_gather(const float* shards, int64_t V, int D, int P, const int32_t* ids, int T,
                                 float* blocks, int32_t* status, hipStream_t stream) {
-  return launch_column<kGather>(shards, blocks, ids, nullptr, T, V, T, 0, D, P, status, stream);
+  return launch_column<kGather>(shards, blocks, ids, nullptr, T, V, T, 0, D, P, nullptr, status, stream);
 }
 
 hipError_t launch_column_assemble(const float* blocks, int64_t C, int64_t row0, int R, int D, int P, float* rows,
                                   hipStream_t stream) {
-  return launch_column<kAssemble>(blocks, rows, nullptr, nullptr, R, C, 0, row0, D, P, nullptr, stream);
+  return launch_column<kAssemble>(blocks, rows, nullptr, nullptr, R, C, 0, row0, D, P, nullptr, nullptr, stream);
 }
 
 }  // namespace emb

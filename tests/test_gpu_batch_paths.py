@@ -150,3 +150,20 @@ def test_split_next_sets(T, T_next, V, law):
     nxt[5::17] = -1
     nxt[6::17] = V
     check_split(ids, nxt, grads_for(T, T, 4, 0.01), V, owners("mod", V, 3), 3)
+
+
+# --------------------------------------------------------------- column packs
+@pytest.mark.parametrize("cap,R,D,P", [(5, 0, 64, 4), (5, 5, 64, 4), (9, 8, 2048, 8), (700, 641, 16, 1), (33, 31, 300, 7),
+                                       (3, 2, 12000, 3)])
+def test_column_pack_counts_and_tiles(cap, R, D, P):
+    # the counts come with the pack; whole and partial tiles, rows wider than a tile, no rows at all
+    rows = grads_for(cap + D, cap, D)
+    blocks, counts = emb.pack_by_column(to_dev(rows), P, num_rows=to_dev(np.array([R], np.int32)),
+                                        out=(torch.zeros(cap * D, device="cuda"),
+                                             torch.full((P,), -7, dtype=torch.int32, device="cuda")))
+    torch.cuda.synchronize()
+    assert host(counts).tolist() == [R] * P
+    off = emb.column_offsets(D, P)
+    for p in range(P):
+        got = host(emb.column_block(blocks, cap, D, P, p))
+        assert np.array_equal(got[:R], rows[:R, off[p]:off[p + 1]]) and not got[R:].any()
