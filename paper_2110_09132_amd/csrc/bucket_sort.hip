@@ -232,6 +232,8 @@ __global__ __launch_bounds__(C::kThreads) void bucket_split_kernel(const int32_t
   // what the later kernels add to starts at zero
   for (int i = tile * NT + tid; i < nred; i += static_cast<int>(gridDim.x) * NT) ws.tile_heads[i] = 0;
   if (tile == 0 && tid == 0) *ws.span_count = 0;
+  if (tile == 0 && ws.zero_counts != nullptr)
+    for (int p = tid; p < ws.P; p += NT) ws.zero_counts[p] = 0;
   // the splitters: every second key of the sorted sample (a sample that takes no part sorts last)
   uint32_t s[kSmp];
 #pragma unroll

@@ -1066,6 +1066,7 @@ __global__ __launch_bounds__(kRedTile) void request_kernel(const uint32_t* __res
                                                            const int32_t* __restrict__ ids,
                                                            int32_t* __restrict__ req_ids,
                                                            int32_t* __restrict__ req_offsets,
+                                                           int32_t* __restrict__ req_counts,
                                                            int32_t* __restrict__ num_unique,
                                                            int32_t* __restrict__ inverse) {
   constexpr int NW = kRedTile / kWave;
@@ -1095,17 +1096,25 @@ __global__ __launch_bounds__(kRedTile) void request_kernel(const uint32_t* __res
   for (int q = 0; q < w; ++q) ubase += wave_heads[q];
   const uint64_t upto = (lane == kWave - 1) ? ~0ull : ((2ull << lane) - 1ull);
   const int u = static_cast<int>(ubase + __popcll(heads & upto)) - 1;
+  // owner p's requests start at row u; with counts (cleared before), the row ends
+  // owner p - 1's count and starts owner p's
+  auto set_offset = [&](int p, int row) {
+    req_offsets[p] = row;
+    if (req_counts == nullptr) return;
+    if (p > 0) atomicAdd(&req_counts[p - 1], row);
+    if (p < ks.G) atomicAdd(&req_counts[p], -row);
+  };
   if (valid && u >= 0 && u < T) {
     if (pos >= 0 && pos < T) inverse[pos] = u;
     if (head) {
       req_ids[u] = static_cast<int32_t>(key & ks.id_mask);
       const int o = min(group_of(key, ks), ks.G);  // owners o_prev < p <= o start here
       const int o_prev = e == 0 ? -1 : group_of(key_prev, ks);
-      for (int p = o_prev + 1; p <= o; ++p) req_offsets[p] = u;
+      for (int p = o_prev + 1; p <= o; ++p) set_offset(p, u);
     }
     if (e + 1 == tv) {
       num_unique[0] = u + 1;
-      for (int p = min(group_of(key, ks), ks.G) + 1; p <= ks.G; ++p) req_offsets[p] = u + 1;
+      for (int p = min(group_of(key, ks), ks.G) + 1; p <= ks.G; ++p) set_offset(p, u + 1);
     }
   }
   if (e == 0 && !valid) {  // no token takes part
@@ -1324,10 +1333,10 @@ bool next_in_lds(int T, int64_t V, const KeySpec& ks, const CoalesceVariant& var
   return small_batch(T, ks) ? var.T_next <= kSmallNextIds : bucket_next_in_lds(V, T, var.T_next);
 }
 
-// full: the radix passes and head counts even for a small batch (the lookup
-// requests read the sorted keys).
+// full: the sort and head counts even for a small batch (the lookup requests
+// read the sorted keys); zero_counts: P words that the bucket sort clears.
 hipError_t sort_chain(const int32_t* ids, int T, int64_t V, int D, const CoalesceVariant& var, void* workspace,
-                      int32_t* status, hipStream_t stream, bool full) {
+                      int32_t* status, hipStream_t stream, bool full, int32_t* zero_counts = nullptr) {
   if (T == 0) return hipSuccess;
   CoalesceWs ws = carve(workspace, T, D, is_split(var) ? var.T_next : -1, V);
   KeySpec ks = key_spec(V, var.row_owner, var.P, is_split(var));
@@ -1351,7 +1360,10 @@ hipError_t sort_chain(const int32_t* ids, int T, int64_t V, int D, const Coalesc
   // a small batch is sorted and summed by one kernel of the reduction half
   if (!full && small_batch(T, ks)) return hipGetLastError();
   if (bucket_sorted(T)) {
-    launch_bucket_sort(ids, T, ks, plan.B, bucket_ws(ws), ws.sort_lb + T, nred, status, stream);
+    BucketWs bws = bucket_ws(ws);
+    bws.zero_counts = zero_counts;
+    bws.P = var.P;
+    launch_bucket_sort(ids, T, ks, plan.B, bws, ws.sort_lb + T, nred, status, stream);
     return hipGetLastError();
   }
   // the key of every token (owner and next-batch lookups once) with the digit
@@ -1484,7 +1496,7 @@ hipError_t launch_lookup_request(const int32_t* ids, int T, int64_t V, const int
   CoalesceVariant var;
   var.row_owner = row_owner;
   var.P = P;
-  const hipError_t e = sort_chain(ids, T, V, 0, var, workspace, status, stream, true);
+  const hipError_t e = sort_chain(ids, T, V, 0, var, workspace, status, stream, true, req_counts);
   if (e != hipSuccess) return e;
   const CoalesceWs ws = carve(workspace, T, 0, -1, V);
   const KeySpec ks = key_spec(V, row_owner, P, false);
@@ -1493,9 +1505,14 @@ hipError_t launch_lookup_request(const int32_t* ids, int T, int64_t V, const int
   const int32_t* vin = nullptr;
   sorted_arrays(ws, plan, T, &kin, &vin);
   const int nred = (T + kRedTile - 1) / kRedTile;
+  // the bucket sort has cleared the counts, which the owners' starts then add to; the
+  // counts by a launch of their own cost a call of 2000 tokens MEASURED
+  const bool counted = bucket_sorted(T);
   hipLaunchKernelGGL(request_kernel, dim3(nred), dim3(kRedTile), 0, stream, kin, vin, ws.n_valid, T, ws.tile_heads, ks,
-                     ids, req_ids, req_offsets, num_unique, inverse);
-  hipLaunchKernelGGL(request_counts_kernel, dim3(1), dim3(1024), 0, stream, req_offsets, req_counts, num_unique, P, 0);
+                     ids, req_ids, req_offsets, counted ? req_counts : nullptr, num_unique, inverse);
+  if (!counted)
+    hipLaunchKernelGGL(request_counts_kernel, dim3(1), dim3(1024), 0, stream, req_offsets, req_counts, num_unique, P,
+                       0);
   return hipGetLastError();
 }
 

@@ -58,6 +58,8 @@ struct BucketWs {
   uint32_t *tmp_keys, *tmp_vals;    // [T] for a bucket that does not fit in LDS
   uint32_t* n_valid;                // tokens that take part
   int32_t* span_count;              // cleared for the reduction
+  int32_t* zero_counts;             // if given: P words cleared for the caller
+  int P;
   uint32_t* tile_heads;             // [nred] first tokens of an id per kRedTile sorted tokens
   // set by the launch, in its words:
   uint32_t* splitters;              // ascending; one of padding at the end
