@@ -511,6 +511,14 @@ struct GradRow<false, 4> {
   }
 };
 template <>
+struct GradRow<false, 2> {
+  using Acc = float2;
+  __device__ static Acc load(const void* g, size_t row, int Dv, int c) {
+    const uint2 h = load_stream(reinterpret_cast<const uint2*>(g) + row * Dv + c);
+    return make_float2(__uint_as_float(h.x), __uint_as_float(h.y));
+  }
+};
+template <>
 struct GradRow<false, 1> {
   using Acc = float;
   __device__ static Acc load(const void* g, size_t row, int Dv, int c) {
@@ -524,6 +532,14 @@ struct GradRow<true, 4> {
     const uint2 h = load_stream(reinterpret_cast<const uint2*>(g) + row * Dv + c);
     return make_float4(__uint_as_float(h.x << 16), __uint_as_float(h.x & 0xFFFF0000u), __uint_as_float(h.y << 16),
                        __uint_as_float(h.y & 0xFFFF0000u));
+  }
+};
+template <>
+struct GradRow<true, 2> {
+  using Acc = float2;
+  __device__ static Acc load(const void* g, size_t row, int Dv, int c) {
+    const uint32_t h = load_stream(reinterpret_cast<const uint32_t*>(g) + row * Dv + c);
+    return make_float2(__uint_as_float(h << 16), __uint_as_float(h & 0xFFFF0000u));
   }
 };
 template <>
@@ -1292,6 +1308,27 @@ int reduce_col_split(int nred, int Dv) {
   return max(1, min(nblocks, want));
 }
 
+// Floats per lane of the reduction: the most that divide the rows (and their
+// addresses), but fewer where the launch would then have less than
+// kReduceMinGroups workgroups, each pulling its 128 rows through one CU (narrower
+// vectors make more column blocks; a column's additions do not change).  Owner-major
+// calls with float4 -> the vectors of this rule: 4000 tokens of 512 floats 27.5 ->
+// 24.4 us, 4000 of 64 24.8 -> 23.4, 8000 of 256 28.3 -> 26.1, 16000 of 256 29.6 ->
+// 28.7; with a limit of 256 also 20000 of 256 (157 workgroups), 30.1 -> 30.8.  A step
+// of 9999 tokens of 300 floats (79 workgroups, 1.2 column blocks): 44.6 -> 43.9.
+constexpr int kReduceMinGroups = 150;
+int reduce_vec(int nred, int D, const void* grad, bool grad_bf16, const float* uniq_grad) {
+  const size_t elem = grad_bf16 ? 2 : 4;
+  for (int vec = 4; vec >= 2; vec /= 2) {
+    if (D % vec != 0 || reinterpret_cast<uintptr_t>(grad) % (vec * elem) != 0 ||
+        reinterpret_cast<uintptr_t>(uniq_grad) % (vec * sizeof(float)) != 0)
+      continue;
+    // full column blocks (a block of few columns loads little)
+    if (static_cast<long long>(nred) * D >= static_cast<long long>(kReduceMinGroups) * kWave * vec) return vec;
+  }
+  return 1;
+}
+
 bool is_split(const CoalesceVariant& var) { return var.row_owner != nullptr && var.T_next >= 0; }
 
 RadixPlan plan_for_call(int64_t V, const CoalesceVariant& var) {
@@ -1467,19 +1504,29 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
                         ws.partial, D,                                                                               \
                         seg_offsets, ws.span_list, ws.span_count, uniq_grad, group_offsets, group_counts, ks.G, T,  \
                         nred)
-  if (vec4) {
-    if (grad_bf16)
-      EMB_REDUCE(true, 4);
-    else
-      EMB_REDUCE(false, 4);
-    EMB_COMBINE(4);
-  } else {
-    if (grad_bf16)
-      EMB_REDUCE(true, 1);
-    else
-      EMB_REDUCE(false, 1);
-    EMB_COMBINE(1);
+  switch (reduce_vec(nred, D, grad, grad_bf16, uniq_grad)) {
+    case 4:
+      if (grad_bf16)
+        EMB_REDUCE(true, 4);
+      else
+        EMB_REDUCE(false, 4);
+      break;
+    case 2:
+      if (grad_bf16)
+        EMB_REDUCE(true, 2);
+      else
+        EMB_REDUCE(false, 2);
+      break;
+    default:
+      if (grad_bf16)
+        EMB_REDUCE(true, 1);
+      else
+        EMB_REDUCE(false, 1);
   }
+  if (vec4)
+    EMB_COMBINE(4);
+  else
+    EMB_COMBINE(1);
 #undef EMB_REDUCE
 #undef EMB_COMBINE
   return hipGetLastError();

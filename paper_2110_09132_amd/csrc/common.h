@@ -41,6 +41,7 @@ __device__ __forceinline__ uint2 load_stream(const uint2* p) {
   const stream_u2 v = __builtin_nontemporal_load(reinterpret_cast<const stream_u2*>(p));
   return make_uint2(v.x, v.y);
 }
+__device__ __forceinline__ uint32_t load_stream(const uint32_t* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ uint16_t load_stream(const uint16_t* p) { return __builtin_nontemporal_load(p); }
 
 // Wave-uniform value as an SGPR (lets the compiler use scalar loads).

@@ -167,3 +167,15 @@ def test_column_pack_counts_and_tiles(cap, R, D, P):
     for p in range(P):
         got = host(emb.column_block(blocks, cap, D, P, p))
         assert np.array_equal(got[:R], rows[:R, off[p]:off[p + 1]]) and not got[R:].any()
+
+
+# -------------------------------------------------------------------- reduction
+@pytest.mark.parametrize("T,D", [(2100, 4), (2100, 6), (2100, 130), (2500, 516), (9000, 258), (9601, 128), (19100, 64),
+                                 (19300, 64)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_reduction_vector_widths(T, D, bf16):
+    # one, two and four floats per lane (few workgroups take narrower vectors), rows that only two
+    # floats divide, ids crossing chunks and workgroups, column blocks with idle lanes
+    V, P = 900, 4
+    ids = ids_for("zipf", T + D, T, V, 1.2)
+    check_by_owner(ids, grads_for(T + D, T, D, 0.01, bf16=bf16), V, owners("mod", V, P), P, bf16=bf16)
