@@ -16,8 +16,14 @@
 namespace emb {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256;  // at most
 constexpr int kRowsInFlight = 8;
+// With fewer waves than this the launch spreads them out: workgroups of one
+// wave (the waves share nothing), and wide rows' column steps over several of
+// them.  2000 rows of 4 KB took 63 workgroups, each pulling 128 KB through one
+// CU: 7.5 -> 6.1 us a call; 4000 8.6 -> 6.9, 8000 15.0 -> 11.7; rows of one column
+// step unchanged.
+constexpr int kSpreadWaves = 1024;
 
 // kWide: rows of more than one column step (Dv > 64).  The wave's column steps
 // and row groups then run as one sequence of tiles, so that the loads of the
@@ -33,8 +39,9 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const VecT* __restrict
   const int lane = static_cast<int>(lane_id());
   const int sub = lane >> log2L;
   const int cl = lane & (L - 1);
-  const int wave = uniform(static_cast<int>(blockIdx.x) * (kThreads / kWave) + static_cast<int>(threadIdx.x / kWave));
-  const int nwaves = static_cast<int>(gridDim.x) * (kThreads / kWave);
+  const int block_waves = static_cast<int>(blockDim.x) / kWave;
+  const int wave = uniform(static_cast<int>(blockIdx.x) * block_waves + static_cast<int>(threadIdx.x / kWave));
+  const int nwaves = static_cast<int>(gridDim.x) * block_waves;
   // rows of this wave: [r0, r1), a multiple of the rows one step covers
   const long long step_rows = static_cast<long long>(rpw) * kRowsInFlight;
   long long per = (static_cast<long long>(T) + nwaves - 1) / nwaves;
@@ -61,14 +68,16 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const VecT* __restrict
         int c, g;
         bool live;
       } A, B;
-      const int nsteps = (Dv + L - 1) / L;
+      // (column steps blockIdx.y, blockIdx.y + gridDim.y, ... of this workgroup)
+      const int part = static_cast<int>(blockIdx.y), parts = static_cast<int>(gridDim.y);
+      const int nsteps = ((Dv + L - 1) / L - part + parts - 1) / parts;
       const int ntiles = nsteps * ngroups;
       int lk = 0, lg = 0, lq = 0;  // the next tile to load
       // a tile past the last one reads row 0 (one cached line) and is not stored
       auto load = [&](Tile& x) {
         x.live = lq < ntiles;
         x.g = x.live ? lg : 0;
-        const int cb = (x.live ? lk : 0) * L;
+        const int cb = (part + (x.live ? lk : 0) * parts) * L;
         x.c = min(cb + cl, Dv - 1);
         const bool cok = cb + cl < Dv;
 #pragma unroll
@@ -146,24 +155,28 @@ hipError_t launch_gather(const float* table, int64_t V, int D, const int32_t* id
                     (reinterpret_cast<uintptr_t>(out) % 16 == 0);
   const int Dv = vec4 ? D / 4 : D;
   const RowLanes rl = row_lanes_for(Dv);
-  const long long rows_per_block = static_cast<long long>(rl.rows_per_wave()) * kRowsInFlight * (kThreads / kWave);
-  const unsigned grid = grid_for((T + rows_per_block - 1) / rows_per_block, kMaxBlocks);
+  const long long rows_per_wave = static_cast<long long>(rl.rows_per_wave()) * kRowsInFlight;
+  const long long waves = (T + rows_per_wave - 1) / rows_per_wave;
   const bool wide = Dv > kWave;
+  const bool spread = waves < kSpreadWaves;
+  const int threads = spread ? kWave : kThreads;
+  const int parts = spread && wide ? static_cast<int>(grid_for(kSpreadWaves / waves, (Dv + kWave - 1) / kWave)) : 1;
+  const dim3 grid(grid_for((waves * kWave + threads - 1) / threads, kMaxBlocks), parts);
   if (vec4) {
     const auto* tv = reinterpret_cast<const float4*>(table);
     auto* ov = reinterpret_cast<float4*>(out);
     if (wide)
-      hipExtLaunchKernelGGL((gather_kernel<float4, true>), dim3(grid), dim3(kThreads), 0, stream, nullptr, done, 0, tv,
+      hipExtLaunchKernelGGL((gather_kernel<float4, true>), grid, dim3(threads), 0, stream, nullptr, done, 0, tv,
                             V, Dv, rl.log2_lanes, ids, T, ov, status);
     else
-      hipExtLaunchKernelGGL((gather_kernel<float4, false>), dim3(grid), dim3(kThreads), 0, stream, nullptr, done, 0, tv,
+      hipExtLaunchKernelGGL((gather_kernel<float4, false>), grid, dim3(threads), 0, stream, nullptr, done, 0, tv,
                             V, Dv, rl.log2_lanes, ids, T, ov, status);
   } else {
     if (wide)
-      hipExtLaunchKernelGGL((gather_kernel<float, true>), dim3(grid), dim3(kThreads), 0, stream, nullptr, done, 0,
+      hipExtLaunchKernelGGL((gather_kernel<float, true>), grid, dim3(threads), 0, stream, nullptr, done, 0,
                             table, V, Dv, rl.log2_lanes, ids, T, out, status);
     else
-      hipExtLaunchKernelGGL((gather_kernel<float, false>), dim3(grid), dim3(kThreads), 0, stream, nullptr, done, 0,
+      hipExtLaunchKernelGGL((gather_kernel<float, false>), grid, dim3(threads), 0, stream, nullptr, done, 0,
                             table, V, Dv, rl.log2_lanes, ids, T, out, status);
   }
   return hipGetLastError();

@@ -179,3 +179,19 @@ def test_reduction_vector_widths(T, D, bf16):
     V, P = 900, 4
     ids = ids_for("zipf", T + D, T, V, 1.2)
     check_by_owner(ids, grads_for(T + D, T, D, 0.01, bf16=bf16), V, owners("mod", V, P), P, bf16=bf16)
+
+
+# ----------------------------------------------------------------------- lookup
+@pytest.mark.parametrize("T,D", [(1, 300), (8, 1024), (9, 259), (63, 2052), (1000, 516), (2047, 260), (8184, 257),
+                                 (8192, 257), (8193, 257), (32768, 4), (500, 12)])
+def test_lookup_spread(T, D):
+    # few waves: one per workgroup, the column steps of wide rows over several; both sides of the limit
+    V = 700
+    W = grads_for(D, V, D)
+    ids = ids_for("uniform", T, T, V)
+    ids[T // 2] = V
+    st = emb.new_status()
+    out = emb.gather(to_dev(W), to_dev(ids), out=torch.full((T, D), 7.0, device="cuda"), dev_status=st)
+    torch.cuda.synchronize()
+    want = np.where((ids < V)[:, None], W[np.minimum(ids, V - 1)], np.float32(0))
+    assert np.array_equal(host(out).view(np.uint32), want.view(np.uint32)) and int(st.item()) == emb.EMB_DEV_ID_OUT_OF_RANGE
