@@ -70,11 +70,11 @@ struct BucketWs {
 // The vertical split's set of next ids is built in LDS by each workgroup of the
 // bucket sort's first kernel (a bit per row), up to these sizes: two launches
 // (clear and insert, 6.5 us with their gaps) against reading the ids once per
-// tile, which costs as much at 20000 ids (split calls, 4096 tokens and next ids:
-// 30.5 -> 27.1 us; 16384: 30.5 -> 28.5 uniform, 31.1 -> 29.4 Zipf; 25000: 29.9 ->
-// 31.3 and 31.2 -> 31.8).
+// tile, which costs as much at 16384 to 20000 ids (split calls, 4096 tokens and
+// next ids: 30.5 -> 27.1 us; 16384: 30.5 -> 28.5, but 44.5 -> 44.8 with rows of
+// 4 KB and ids that are not in the caches; 25000: 29.9 -> 31.3).
 constexpr int64_t kLdsNextRows = 1 << 18;
-constexpr int kLdsNextIds = 1 << 14;
+constexpr int kLdsNextIds = 1 << 13;
 inline bool bucket_next_in_lds(int64_t V, int T, int T_next) {
   return T <= 1 << 17 && V <= kLdsNextRows && T_next <= kLdsNextIds;
 }

@@ -140,7 +140,7 @@ def test_pack_places(T, D, P):
 # ------------------------------------------------------------------------ split
 @pytest.mark.parametrize("T,T_next,V", [
     (300, 1, 1000), (1000, 2048, 900000), (2048, 2048, 1 << 25), (2000, 2049, 5000),  # small batches
-    (2049, 1, 1 << 18), (5000, 16384, 1 << 18), (5000, 16385, 1 << 18), (5000, 700, (1 << 18) + 1), (3000, 8191, 33),
+    (2049, 1, 1 << 18), (5000, 8192, 1 << 18), (5000, 8193, 1 << 18), (5000, 700, (1 << 18) + 1), (3000, 8191, 33),
     (131072, 9000, 40000), (131073, 9000, 40000)])
 @pytest.mark.parametrize("law", ["zipf", "uniform"])
 def test_split_next_sets(T, T_next, V, law):
@@ -195,3 +195,29 @@ def test_lookup_spread(T, D):
     torch.cuda.synchronize()
     want = np.where((ids < V)[:, None], W[np.minimum(ids, V - 1)], np.float32(0))
     assert np.array_equal(host(out).view(np.uint32), want.view(np.uint32)) and int(st.item()) == emb.EMB_DEV_ID_OUT_OF_RANGE
+
+
+# --------------------------------------------------------------------- exchange
+@pytest.mark.parametrize("P", [1, 3, 31, 32, 33, 64])
+@pytest.mark.parametrize("cap,D", [(1, 4), (40, 0), (333, 5), (500, 132)])
+def test_exchange_destinations(P, cap, D):
+    # destinations worked out by every workgroup (up to 32 workers) or by a launch of their own; empty
+    # blocks, senders with nothing to send, ids alone
+    rng = np.random.default_rng(P * 1000 + cap)
+    offs = np.zeros((P, P + 1), np.int32)
+    for w in range(P):
+        n = 0 if w % 5 == 3 else int(rng.integers(0, cap + 1))
+        offs[w, 1:] = np.sort(np.r_[rng.integers(0, n + 1, P - 1), n])
+    ids = rng.integers(0, 1 << 30, (P, cap)).astype(np.int32)
+    rows = rng.standard_normal((P, cap, max(D, 1))).astype(np.float32)
+    r_ids, r_rows, r_offs, total = emb.exchange_simulated(to_dev(ids), to_dev(rows) if D else None, to_dev(offs))
+    torch.cuda.synchronize()
+    want = [(w, slice(offs[w, p], offs[w, p + 1])) for p in range(P) for w in range(P)]
+    n = int(offs[:, P].sum())
+    starts = np.cumsum([0] + [offs[w, p + 1] - offs[w, p] for p in range(P) for w in range(P)])
+    got = host(r_offs)
+    assert int(total.item()) == n and np.array_equal(got[:, :P].ravel(), starts[:-1])
+    assert np.array_equal(got[:, P], starts[P::P])
+    assert np.array_equal(host(r_ids)[:n], np.concatenate([ids[w, s] for w, s in want]))
+    if D:
+        assert np.array_equal(host(r_rows)[:n], np.concatenate([rows[w, s] for w, s in want]))
