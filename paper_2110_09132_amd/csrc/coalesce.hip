@@ -1552,8 +1552,10 @@ hipError_t launch_lookup_request(const int32_t* ids, int T, int64_t V, const int
   const int32_t* vin = nullptr;
   sorted_arrays(ws, plan, T, &kin, &vin);
   const int nred = (T + kRedTile - 1) / kRedTile;
-  // the bucket sort has cleared the counts, which the owners' starts then add to; the
-  // counts by a launch of their own cost a call of 2000 tokens MEASURED
+  // the bucket sort has cleared the counts, which the owners' starts then add to; a
+  // launch of their own for them cost more (2000 tokens: 19.5 -> 16 to 18 us a call;
+  // 65536: 20.7 -> 18.8), and so did an addition per wave and owner (1024 of them on
+  // one cache line: 29 us at 65536)
   const bool counted = bucket_sorted(T);
   hipLaunchKernelGGL(request_kernel, dim3(nred), dim3(kRedTile), 0, stream, kin, vin, ws.n_valid, T, ws.tile_heads, ks,
                      ids, req_ids, req_offsets, counted ? req_counts : nullptr, num_unique, inverse);

@@ -26,12 +26,12 @@ struct CoalesceVariant {
 
 // Workspace size (T_next < 0: no split); it does not depend on the other choices.
 size_t coalesce_workspace_bytes(int T, int D, int T_next, int64_t V);
-bool coalesce_by_owner_supported(int64_t V, int P, bool split);  // the composite keys fit the radix passes
+bool coalesce_by_owner_supported(int64_t V, int P, bool split);  // the composite keys fit 32 bits
 // The two halves of launch_coalesce, for schedules that run them on different
 // streams (same ids, workspace and variant; the reduce half must follow the
 // sort half).  A batch of at most 2048 tokens is sorted and summed by one
-// kernel of the reduce half (the sort half then only builds the next-id set
-// of the split).  done (may be null): an event attached to the reduce half's
+// kernel of the reduce half (the sort half then builds at most the next-id set
+// of the split, where that is not formed in LDS).  done (may be null): an event attached to the reduce half's
 // last kernel.
 hipError_t launch_coalesce_sort(const int32_t* ids, int T, int64_t V, int D, const CoalesceVariant& var,
                                 void* workspace, int32_t* status, hipStream_t stream);
