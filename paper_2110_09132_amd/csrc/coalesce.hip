@@ -1102,7 +1102,16 @@ __global__ __launch_bounds__(kRedTile) void request_kernel(const uint32_t* __res
   const uint64_t heads = __ballot(head);
   if (lane == 0) wave_heads[w] = static_cast<uint32_t>(__popcll(heads));
   uint32_t before = 0;
-  for (int t = static_cast<int>(threadIdx.x); t < tile; t += kRedTile) before += tile_heads[t];
+  // eight loads in flight (one by one, the last of 512 workgroups waited for four
+  // round trips: requests of 65536 tokens 18.9 -> 18.1 us a call, 262144 Zipf 40.1 ->
+  // 37.4, 524288 63.1 -> 58.3)
+  for (int t0 = static_cast<int>(threadIdx.x); t0 < tile; t0 += kRedTile * kLoadsInFlight) {
+    uint32_t v[kLoadsInFlight];
+#pragma unroll
+    for (int q = 0; q < kLoadsInFlight; ++q) v[q] = tile_heads[min(t0 + q * kRedTile, tile - 1)];
+#pragma unroll
+    for (int q = 0; q < kLoadsInFlight; ++q) before += t0 + q * kRedTile < tile ? v[q] : 0u;
+  }
   before = wave_sum(before);
   if (lane == 0) red[w] = before;
   __syncthreads();
