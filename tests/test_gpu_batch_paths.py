@@ -93,6 +93,17 @@ def test_lookup_request_sizes(T):
     check_request(ids, V, own, P)
 
 
+@pytest.mark.parametrize("used", [[0], [1023], [511], [0, 1023], [1, 2, 700], [5, 1022]])
+@pytest.mark.parametrize("T", [1, 3, 200, 70000])
+def test_lookup_request_owners_without_requests(used, T):
+    # runs of owners that nothing is asked of, at either end and between: only a run's ends change the
+    # counts
+    V, P = 1 << 14, 1024
+    rng = np.random.default_rng(T)
+    ids = (rng.choice(used, T) + P * rng.integers(0, V // P, T)).astype(np.int32)
+    check_request(ids, V, owners("mod", V, P), P)
+
+
 @pytest.mark.parametrize("count", [0, 1, 3000, 139999])
 def test_device_count_over_all_samples(count):
     # a device-side token count: the samples come from the tokens that exist
