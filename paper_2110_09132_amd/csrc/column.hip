@@ -136,11 +136,26 @@ __global__ __launch_bounds__(kThreads) void column_kernel(const VecT* __restrict
 // the rows of a tile start in different banks.  Threads issue kUnroll loads
 // before they store.
 constexpr int kTileUnits = 1024;  // units per tile (16 KB of float4)
-// The pack of float4 takes half of that: more, smaller workgroups, since each
-// waits for its loads before its first store (12288 rows of 4 KB, 8 owners: 25.9
-// -> 22.7 us; 49152 of 1 KB, 16 owners: 24.5 -> 23.5; single floats, whose
-// runs per owner are short, were slower so: 10.8 -> 13.4 at 128 floats, 12 owners).
+// The pack of float4 takes half of that where pack_half_tiles allows it: more,
+// smaller workgroups, since each waits for its loads before its first store.
 constexpr int kPackUnits = 512;
+// Half a tile has half as long a run per owner, and a wave stores a run at a time:
+// past about 12 owners the runs leave most of a wave's lanes idle.  Calls with 1024 ->
+// 512 units, from HBM / from the caches:
+//   up to 12 owners  8000 rows of 4 KB, 8 owners 16.0 -> 15.6 / 11.4 -> 12.4 us; 30000,
+//                    48.9 -> 46.3 / 37.2 both; 3000 of 1 KB, 8 owners 5.5 -> 4.5
+//   16 owners        8000 of 4 KB 16.1 -> 17.0 / 12.2 -> 14.5; but few workgroups, 3000
+//                    of 1 KB 5.8 -> 5.1, and much data, 30000 of 4 KB 49.7 -> 47.0
+//   32 owners        1000 of 1 KB 6.3 -> 5.4; 16000 of 4 KB 31.5 -> 35.3
+//   64 owners        30000 of 4 KB 62.7 -> 101.9
+// A half tile of one row pays only where it is nearly full and a whole number of
+// waves: 30000 rows of 1536 floats, 8 owners 70.2 -> 66.8; of 1600, 78.2 -> 78.7; of 1200,
+// 4 owners 54.0 -> 58.5 (from the caches).
+bool pack_half_tiles(int cap, int Dv, int P) {
+  const long long units = static_cast<long long>(cap) * Dv;
+  if (Dv > kPackUnits / 2 && (Dv < kPackUnits * 3 / 4 || Dv % kWave != 0)) return false;
+  return P <= 12 || (P <= 32 && units * P < 8 << 20) || (P <= 20 && units >= 15 << 18);
+}
 constexpr int kUnroll = 4;
 constexpr int kLdsPad = 1;
 
@@ -256,7 +271,7 @@ hipError_t launch_column(const float* src, float* dst, const int32_t* ids, const
   // tiles of up to kTileUnits units (at least one row); rows too wide for a
   // 32 KB tile take the row-per-lanes kernel
   const size_t unit = vec4 ? sizeof(float4) : sizeof(float);
-  const int TR = max(1, (kMode == kPack && vec4 ? kPackUnits : kTileUnits) / Dv);
+  const int TR = max(1, (kMode == kPack && vec4 && pack_half_tiles(cap, Dv, P) ? kPackUnits : kTileUnits) / Dv);
   const size_t lds = static_cast<size_t>(TR) * (Dv + kLdsPad) * unit;
   if (lds <= 32768) {
     const unsigned tiles = static_cast<unsigned>((static_cast<long long>(cap) + TR - 1) / TR);

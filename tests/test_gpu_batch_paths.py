@@ -165,7 +165,13 @@ def test_split_next_sets(T, T_next, V, law):
 
 # --------------------------------------------------------------- column packs
 @pytest.mark.parametrize("cap,R,D,P", [(5, 0, 64, 4), (5, 5, 64, 4), (9, 8, 2048, 8), (700, 641, 16, 1), (33, 31, 300, 7),
-                                       (3, 2, 12000, 3)])
+                                       (3, 2, 12000, 3),
+                                       # both sides of the rule on the tile's size: owners, units, row width
+                                       (700, 699, 96, 12), (700, 699, 104, 13), (4096, 4095, 512, 16),
+                                       (4097, 4096, 512, 16), (30721, 30720, 512, 16), (30000, 29999, 512, 16),
+                                       (2048, 2047, 512, 32), (2049, 2048, 512, 32), (50, 49, 528, 33),
+                                       (37, 36, 1024, 8), (37, 36, 1028, 1), (37, 36, 1532, 1), (37, 36, 1536, 8),
+                                       (37, 36, 1540, 1), (37, 36, 1600, 8)])
 def test_column_pack_counts_and_tiles(cap, R, D, P):
     # the counts come with the pack; whole and partial tiles, rows wider than a tile, no rows at all
     rows = grads_for(cap + D, cap, D)
