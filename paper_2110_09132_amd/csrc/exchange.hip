@@ -57,13 +57,24 @@ __global__ __launch_bounds__(kThreads) void exchange_offsets_kernel(const int32_
   if (p == 0) *recv_total = static_cast<int32_t>(all);
 }
 
-// Workers up to which exchange_rows works out the destinations itself: a word or
-// four per thread to load, and P of them to add up.
+// exchange_rows works out the destinations itself for up to this many workers (a
+// word or four per thread to load, and P of them to add up), and while its
+// workgroups together read at most kFusedWords block sizes.  Where they read more, a
+// launch of its own costs less: 32 workers x 50000 half-filled rows of 512 bytes,
+// 25024 workgroups: 191 us with the destinations in each, 179 without; 20000 rows of
+// 1 KB, 155 against 149; 12000 of 512 bytes, 6016 workgroups, 39.6 against 48.2.
 constexpr int kFusedWorkers = 32;
+constexpr long long kFusedWords = 8 << 20;
+// In a launch of this many workgroups one that has no row first looks whether it has
+// (8 workers x 130000 half-filled rows of 1 KB, 32504 workgroups: 236 -> 202 us); in
+// smaller ones that round trip costs more (32 x 40000 half-filled rows of 128 bytes,
+// 5024 workgroups: 36.6 -> 38.1).
+constexpr unsigned kManyGroups = 8192;
 
 // Row k of sender w (k < its sent rows) goes to receiver p, the owner block
 // holding k, at recv_offsets[p][w] + (k - send_offsets[w][p]).  L lanes per row.
-template <typename VecT, bool kFused>
+// kFused: the destinations are worked out here; kLook: see kManyGroups.
+template <typename VecT, bool kFused, bool kLook>
 __global__ __launch_bounds__(kRowThreads) void exchange_rows_kernel(
     const int32_t* __restrict__ send_ids, const VecT* __restrict__ send_rows, const int32_t* __restrict__ send_offsets,
     int P, int cap, int Dv, int log2L, int32_t* __restrict__ recv_offsets, int32_t* __restrict__ recv_total,
@@ -79,6 +90,9 @@ __global__ __launch_bounds__(kRowThreads) void exchange_rows_kernel(
   const int cl = static_cast<int>(lane_id()) & (L - 1);
   const int w = blockIdx.y;  // the sender
   const int32_t* o = send_offsets + static_cast<size_t>(w) * (P + 1);
+  const long long step = static_cast<long long>(rpw) * kRowsInFlight;
+  if (kLook && blockIdx.x > 0 && blockIdx.x * (kRowThreads / kWave) * step >= min(max(o[P], 0), cap))
+    return;  // no row for this workgroup (the first one leaves recv_offsets all the same)
   for (int p = threadIdx.x; p <= P; p += kRowThreads) {
     s_o[p] = o[p];
     if (p < P) {
@@ -122,7 +136,6 @@ __global__ __launch_bounds__(kRowThreads) void exchange_rows_kernel(
   const int sent = min(max(s_o[P], 0), cap);
   const long long wave = (static_cast<long long>(blockIdx.x) * kRowThreads + threadIdx.x) / kWave;
   const long long nwaves = static_cast<long long>(gridDim.x) * (kRowThreads / kWave);
-  const long long step = static_cast<long long>(rpw) * kRowsInFlight;
   for (long long r0 = wave * step; r0 < sent; r0 += nwaves * step) {
     int64_t dst[kRowsInFlight];
     int64_t src[kRowsInFlight];
@@ -162,32 +175,36 @@ __global__ __launch_bounds__(kRowThreads) void exchange_rows_kernel(
 hipError_t launch_exchange(const int32_t* send_ids, const float* send_rows, const int32_t* send_offsets, int P,
                            int cap, int D, int32_t* recv_ids, float* recv_rows, int32_t* recv_offsets,
                            int32_t* recv_total, hipStream_t stream) {
-  const bool fused = P <= kFusedWorkers && cap > 0;
-  if (!fused)
-    hipLaunchKernelGGL(exchange_offsets_kernel, dim3(1), dim3(kThreads), 0, stream, send_offsets, P, cap, recv_offsets,
-                       recv_total);
-  if (cap == 0) return hipGetLastError();
   const auto al16 = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
   const bool vec4 = (D % 4 == 0) && al16(send_rows) && al16(recv_rows);
   const int Dv = vec4 ? D / 4 : D;
   const RowLanes rl = row_lanes_for(Dv);
   const long long rows_per_block = static_cast<long long>(rl.rows_per_wave()) * kRowsInFlight * (kRowThreads / kWave);
   const dim3 grid(grid_for((cap + rows_per_block - 1) / rows_per_block, 65535), P);
-#define EMB_EXCHANGE(VT, FUSED)                                                                                     \
-  hipLaunchKernelGGL((exchange_rows_kernel<VT, FUSED>), grid, dim3(kRowThreads), 0, stream, send_ids,               \
+  const bool look = grid.x * grid.y >= kManyGroups;
+  const bool fused = cap > 0 && P <= kFusedWorkers && static_cast<long long>(grid.x) * P * P * P <= kFusedWords;
+  if (!fused)
+    hipLaunchKernelGGL(exchange_offsets_kernel, dim3(1), dim3(kThreads), 0, stream, send_offsets, P, cap, recv_offsets,
+                       recv_total);
+  if (cap == 0) return hipGetLastError();
+#define EMB_EXCHANGE(VT, FUSED, LOOK)                                                                               \
+  hipLaunchKernelGGL((exchange_rows_kernel<VT, FUSED, LOOK>), grid, dim3(kRowThreads), 0, stream, send_ids,         \
                      reinterpret_cast<const VT*>(send_rows), send_offsets, P, cap, Dv, rl.log2_lanes, recv_offsets, \
                      recv_total, recv_ids, reinterpret_cast<VT*>(recv_rows))
-  if (vec4) {
-    if (fused)
-      EMB_EXCHANGE(float4, true);
-    else
-      EMB_EXCHANGE(float4, false);
-  } else {
-    if (fused)
-      EMB_EXCHANGE(float, true);
-    else
-      EMB_EXCHANGE(float, false);
-  }
+#define EMB_EXCHANGE_V(VT)                        \
+  do {                                            \
+    if (fused && look)                            \
+      EMB_EXCHANGE(VT, true, true);               \
+    else if (fused)                               \
+      EMB_EXCHANGE(VT, true, false);              \
+    else                                          \
+      EMB_EXCHANGE(VT, false, false);             \
+  } while (0)
+  if (vec4)
+    EMB_EXCHANGE_V(float4);
+  else
+    EMB_EXCHANGE_V(float);
+#undef EMB_EXCHANGE_V
 #undef EMB_EXCHANGE
   return hipGetLastError();
 }

@@ -215,8 +215,11 @@ def test_lookup_spread(T, D):
 
 
 # --------------------------------------------------------------------- exchange
-@pytest.mark.parametrize("P", [1, 3, 31, 32, 33, 64])
-@pytest.mark.parametrize("cap,D", [(1, 4), (40, 0), (333, 5), (500, 132)])
+@pytest.mark.parametrize("P,cap,D", [(P, cap, D) for P in (1, 3, 31, 32, 33, 64)
+                                     for cap, D in ((1, 4), (40, 0), (333, 5), (500, 132))] +
+                         # workgroups without rows leave early from 8192 workgroups on; the most block
+                         # sizes that the workgroups read themselves, and one workgroup per sender more
+                         [(8, 32736, 33), (8, 32737, 33), (32, 8192, 33), (32, 8193, 33)])
 def test_exchange_destinations(P, cap, D):
     # destinations worked out by every workgroup (up to 32 workers) or by a launch of their own; empty
     # blocks, senders with nothing to send, ids alone
