@@ -19,10 +19,14 @@ namespace {
 constexpr int kThreads = 256;  // at most
 constexpr int kRowsInFlight = 8;
 // With fewer waves than this the launch spreads them out: workgroups of one
-// wave (the waves share nothing), and wide rows' column steps over several of
-// them.  2000 rows of 4 KB took 63 workgroups, each pulling 128 KB through one
-// CU: 7.5 -> 6.1 us a call; 4000 8.6 -> 6.9, 8000 15.0 -> 11.7; rows of one column
-// step unchanged.
+// wave, and wide rows' column steps over several of them.  2000 rows of 4 KB took
+// 63 workgroups, each pulling 128 KB through one CU: 7.5 -> 6.1 us a call; 4000
+// 8.6 -> 6.9, 8000 15.0 -> 11.7; 4200 rows of 256 bytes 4.0 -> 3.8.
+// Rows that are not whole 128-byte lines share a line with the next wave's rows,
+// which workgroups of one wave put on another XCD, whose L2 then writes its part of
+// that line by itself: such rows are spread only where the column steps are split
+// too, which pays all the same (3000 rows of 2053 floats 37.7 -> 22.1 us; but 5000 of
+// 2052 13.5 -> 14.4, 5000 of 33 4.1 -> 4.4 with one wave per workgroup).
 constexpr int kSpreadWaves = 1024;
 
 // kWide: rows of more than one column step (Dv > 64).  The wave's column steps
@@ -158,7 +162,8 @@ hipError_t launch_gather(const float* table, int64_t V, int D, const int32_t* id
   const long long rows_per_wave = static_cast<long long>(rl.rows_per_wave()) * kRowsInFlight;
   const long long waves = (T + rows_per_wave - 1) / rows_per_wave;
   const bool wide = Dv > kWave;
-  const bool spread = waves < kSpreadWaves;
+  const bool lines = (static_cast<size_t>(D) * sizeof(float)) % 128 == 0;
+  const bool spread = waves < kSpreadWaves && (lines || (wide && 2 * waves <= kSpreadWaves));
   const int threads = spread ? kWave : kThreads;
   const int parts = spread && wide ? static_cast<int>(grid_for(kSpreadWaves / waves, (Dv + kWave - 1) / kWave)) : 1;
   const dim3 grid(grid_for((waves * kWave + threads - 1) / threads, kMaxBlocks), parts);

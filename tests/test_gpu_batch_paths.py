@@ -200,9 +200,12 @@ def test_reduction_vector_widths(T, D, bf16):
 
 # ----------------------------------------------------------------------- lookup
 @pytest.mark.parametrize("T,D", [(1, 300), (8, 1024), (9, 259), (63, 2052), (1000, 516), (2047, 260), (8184, 257),
-                                 (8192, 257), (8193, 257), (32768, 4), (500, 12)])
+                                 (8192, 257), (8193, 257), (32768, 4), (500, 12),
+                                 # rows of whole lines and others, narrow and wide, about half the limit's waves
+                                 (700, 32), (700, 33), (4096, 288), (4097, 288), (4096, 260), (4097, 260),
+                                 (4097, 65), (8184, 64), (8193, 64)])
 def test_lookup_spread(T, D):
-    # few waves: one per workgroup, the column steps of wide rows over several; both sides of the limit
+    # few waves: one per workgroup, the column steps of wide rows over several; both sides of the limits
     V = 700
     W = grads_for(D, V, D)
     ids = ids_for("uniform", T, T, V)
