@@ -827,7 +827,13 @@ __global__ __launch_bounds__(kCombineThreads) void seg_combine_kernel(const floa
 // order (a plain sorted-order sum here), within the same bound.
 // What bounds it is latency (stamps, 2000 x 1024, Zipf ids): keys 0.8 us, two
 // sort passes 6.5, segments 1.7, the staging 4, the sums 4.2 (a row of 170
-// tokens; 8.0 with clamped reads that waited for each block of eight).
+// tokens; 8.0 with clamped reads that waited for each block of eight).  The sort's
+// ballots run over the digits' own bits: unrolled over the nine a digit may have
+// they cost a 15-bit key's passes 1.4 us more (1500 tokens).
+// Narrow rows (at most half the vectors of a slice) take the lanes they need, so
+// that more segments are summed at once: their number, not their length, counts
+// where most ids are distinct.  512 distinct rows of one float 17.2 -> 7.3 us a
+// call, 1024 15.8 -> 8.5, 2048 20.6 -> 13.1; 2048 of 4 floats 17.0 -> 14.5.
 // Measured per training step of 2000 tokens with rows of 1024 floats: 299 us
 // with one workgroup summing every column (the kernel 276 us), 39 us with
 // a workgroup per slice; 512 tokens of 64 floats, the kernel: 12.9 -> 10.2 us.
@@ -872,18 +878,25 @@ __device__ __forceinline__ bool lds_set_has(const uint32_t* set, uint32_t id) {
   return false;
 }
 
-template <bool BF16, int VEC, int NT, int IT>
+// NARROW: rows of at most half the vectors of a slice, which take 2^narrow_log2
+// lanes each (all of a row in one slice).
+template <bool BF16, int VEC, int NT, int IT, bool NARROW>
 __global__ __launch_bounds__(NT) void small_coalesce_kernel(
     const int32_t* __restrict__ ids, int T, KeySpec ks, int npass, int bits, const void* __restrict__ grad, int D,
     int32_t* __restrict__ uniq_ids, int32_t* __restrict__ seg_offsets, int32_t* __restrict__ num_unique,
     float* __restrict__ uniq_grad, int32_t* __restrict__ group_counts, int32_t* __restrict__ group_offsets,
-    int32_t* status) {
+    int narrow_log2, int32_t* status) {
   constexpr int NW = NT / kWave, kMax = NT * IT, kBins = 1 << kSmallDigit;
   using Row = GradRow<BF16, VEC>;
   using Acc = typename Row::Acc;
-  constexpr int L = small_slice(kMax, VEC);
+  constexpr int kSlice = small_slice(kMax, VEC);
+  const int L = NARROW ? 1 << narrow_log2 : kSlice;
+  // vectors per staged row, known to the compiler whatever the lanes; narrow rows are
+  // padded so that the segments that a wave reads together lie in different banks
+  constexpr int kRow = NARROW ? kSlice / 2 + 1 : kSlice;
+  static_assert(kRow <= kSlice, "the padded rows fit the staging area");
   static_assert(NW * kBins * sizeof(uint32_t) <= kSmallStage, "the sort's counters fit the staging area");
-  static_assert(NT % L == 0 && kMax * L * sizeof(Acc) == kSmallStage, "whole rows per staging round");
+  static_assert(NT % kSlice == 0 && kMax * kSlice * sizeof(Acc) == kSmallStage, "whole rows per staging round");
   __shared__ __align__(16) unsigned char stage_s[kSmallStage];  // the sort's counters, then the rows' slices
   __shared__ uint32_t key_s[2][kMax];
   __shared__ int32_t pos_s[2][kMax];
@@ -954,7 +967,7 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
     }
 #pragma unroll
     for (int r = 0; r < IT; ++r) dig[r] = valid[r] ? (key[r] >> (bits * p)) & dmask : 0u;
-    n = static_cast<int>(tile_stable_rank<NT, IT, kSmallDigit>(dig, valid, 1 << bits, bits, cnt, dstart, wsum, lpos));
+    n = static_cast<int>(tile_stable_rank<NT, IT>(dig, valid, 1 << bits, bits, cnt, dstart, wsum, lpos));
     cur ^= 1;
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
@@ -1007,22 +1020,30 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
   const int x = static_cast<int>(blockIdx.x) % kXcds;
   const int cl = static_cast<int>(threadIdx.x) % L;
   const int grp = static_cast<int>(threadIdx.x) / L;
+  const int ngrp = NT / L;  // rows per staging round, and segments summed at once
+  constexpr int kLoads = IT * (NARROW ? kSlice / 2 : kSlice);
   Acc* out = reinterpret_cast<Acc*>(uniq_grad);
   for (int i = static_cast<int>(blockIdx.x) / kXcds; i < per_xcd; i += static_cast<int>(gridDim.x) / kXcds) {
     const int c = (x * per_xcd + i) * L + cl;
     if (c - cl >= Dv) break;  // past the last slice (uniform)
     const int cc = min(c, Dv - 1);
-    Acc g[IT * L];
+    int32_t at[kLoads];
 #pragma unroll
-    for (int k = 0; k < IT * L; ++k)
-      g[k] = Row::load(grad, static_cast<size_t>(sp[min(grp + k * (NT / L), n - 1)]), Dv, cc);
+    for (int k = 0; k < kLoads; ++k) at[k] = sp[min(grp + k * ngrp, n - 1)];
+    Acc g[kLoads];
 #pragma unroll
-    for (int k = 0; k < IT * L; ++k) stage[static_cast<int>(threadIdx.x) + k * NT] = g[k];
+    for (int k = 0; k < kLoads; ++k)
+      if (!NARROW || k < IT * L) g[k] = Row::load(grad, static_cast<size_t>(at[k]), Dv, cc);
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k)
+      if (!NARROW || k < IT * L) stage[(grp + k * ngrp) * kRow + cl] = g[k];
     __syncthreads();
-    for (int u = grp; u < U; u += NT / L) {
-      const int S = sstart[u], E = sstart[u + 1];
-      const Acc* row = stage + S * L + cl;
+    int S = sstart[min(grp, U)], E = sstart[min(grp + 1, U)];
+    for (int u = grp; u < U; u += ngrp) {
+      const Acc* row = stage + S * kRow + cl;
       const int len = E - S;
+      S = sstart[min(u + ngrp, U)];  // the next segment's bounds, beside this one's rows
+      E = sstart[min(u + ngrp + 1, U)];
       Acc acc = Acc{};
       // a long segment is a chain of additions: the next eight rows are read while
       // the current eight are added (two buffers in turn, no clamps or branches)
@@ -1030,7 +1051,7 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
       Acc va[kSmallUnroll], vb[kSmallUnroll];
       auto read = [&](Acc(&v)[kSmallUnroll], int i) {
 #pragma unroll
-        for (int k = 0; k < kSmallUnroll; ++k) v[k] = row[(i * kSmallUnroll + k) * L];
+        for (int k = 0; k < kSmallUnroll; ++k) v[k] = row[(i * kSmallUnroll + k) * kRow];
       };
       auto add = [&](const Acc(&v)[kSmallUnroll]) {
 #pragma unroll
@@ -1053,16 +1074,26 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
           add(va);
         }
       }
-      const int done = blocks * kSmallUnroll;
-      if (done < len) {
+      // the rest by fours, twos and ones, each read only where it is there
+      const int done = blocks * kSmallUnroll, rest = len - done;
+      static_assert(kSmallUnroll == 8, "fours, twos and ones");
+      if (rest & 4)
 #pragma unroll
-        for (int k = 0; k < kSmallUnroll - 1; ++k) va[k] = row[min(done + k, len - 1) * L];
+        for (int k = 0; k < 4; ++k) va[k] = row[(done + k) * kRow];
+      if (rest & 2)
 #pragma unroll
-        for (int k = 0; k < kSmallUnroll - 1; ++k)
-          if (done + k < len) acc += va[k];
-      }
+        for (int k = 0; k < 2; ++k) vb[k] = row[(done + (rest & 4) + k) * kRow];
+      if (rest & 1) vb[2] = row[(done + (rest & 6)) * kRow];
+      if (rest & 4)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc += va[k];
+      if (rest & 2)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) acc += vb[k];
+      if (rest & 1) acc += vb[2];
       if (c < Dv) out[static_cast<size_t>(u) * Dv + c] = acc;
     }
+    if (NARROW) break;  // one slice
     __syncthreads();  // the next slice overwrites the staged rows
   }
 }
@@ -1466,10 +1497,19 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
                     (reinterpret_cast<uintptr_t>(uniq_grad) % 16 == 0);
     const int Dv = v4 ? D / 4 : D;
     // the fewest threads and keys per thread that hold the batch: shorter passes
-#define EMB_SMALL_N(BF, VC, NTH, ITM)                                                                               \
-  hipExtLaunchKernelGGL((small_coalesce_kernel<BF, VC, NTH, ITM>), dim3(small_blocks(Dv, small_slice(NTH * ITM, VC))), \
-                        dim3(NTH), 0, stream, nullptr, done, 0, ids, T, kss, npass, bits, grad, D, uniq_ids,        \
-                        seg_offsets, num_unique, uniq_grad, group_counts, group_offsets, status)
+    // rows of at most half a slice take only the lanes they need
+#define EMB_SMALL_K(BF, VC, NTH, ITM, NARROW)                                                                       \
+  hipExtLaunchKernelGGL((small_coalesce_kernel<BF, VC, NTH, ITM, NARROW>),                                          \
+                        dim3(small_blocks(Dv, small_slice(NTH * ITM, VC))), dim3(NTH), 0, stream, nullptr, done, 0, \
+                        ids, T, kss, npass, bits, grad, D, uniq_ids, seg_offsets, num_unique, uniq_grad,            \
+                        group_counts, group_offsets, row_lanes_for(Dv).log2_lanes, status)
+#define EMB_SMALL_N(BF, VC, NTH, ITM)                 \
+  do {                                                \
+    if (2 * Dv <= small_slice(NTH * ITM, VC))         \
+      EMB_SMALL_K(BF, VC, NTH, ITM, true);            \
+    else                                              \
+      EMB_SMALL_K(BF, VC, NTH, ITM, false);           \
+  } while (0)
 #define EMB_SMALL(BF, VC)               \
   do {                                  \
     if (T <= 512)                       \
@@ -1493,6 +1533,7 @@ hipError_t launch_coalesce_reduce(const int32_t* ids, int T, const void* grad, b
     }
 #undef EMB_SMALL
 #undef EMB_SMALL_N
+#undef EMB_SMALL_K
     return hipGetLastError();
   }
   CoalesceWs ws = carve(workspace, T, D, -1, V);  // the next-id set, if any, lies past everything used here

@@ -33,6 +33,20 @@ def test_small_batches_of_wide_rows(T, D):
     check_by_owner(ids, grads_for(T + D, T, D, 0.01), V, owners("range", V, P), P)
 
 
+@pytest.mark.parametrize("T,D", [(512, 1), (511, 3), (300, 15), (512, 17), (512, 16), (512, 20), (1024, 1), (1023, 7),
+                                 (1024, 9), (1024, 8), (1024, 12), (2048, 1), (2047, 3), (2048, 5), (2048, 4), (1100, 8)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_small_batches_of_narrow_rows(T, D, bf16):
+    # both sides of half a slice's vectors, for each kernel's slice; ids of 1 to 18 tokens, so that every
+    # remainder of the sums' blocks of eight occurs, and ids of one token
+    V, P = 3000, 2
+    rng = np.random.default_rng(T + D)
+    ids = np.repeat(np.arange(T, dtype=np.int32), np.resize(np.r_[np.arange(1, 19), 1, 1, 1], T))[:T]
+    ids = rng.permutation(V)[:T][ids % V].astype(np.int32) if T < V else ids
+    rng.shuffle(ids)
+    check_by_owner(ids, grads_for(T * D, T, D, 0.01, bf16=bf16), V, owners("mod", V, P), P, bf16=bf16)
+
+
 # ------------------------------------------------------------------ bucket sort
 def sample_tokens(n, T):
     """The tokens the bucket sort samples (sample_token in bucket_sort.hip)."""
