@@ -1358,11 +1358,14 @@ int reduce_col_split(int nred, int Dv) {
 // 24.4 us, 4000 of 64 24.8 -> 23.4, 8000 of 256 28.3 -> 26.1, 16000 of 256 29.6 ->
 // 28.7; with a limit of 256 also 20000 of 256 (157 workgroups), 30.1 -> 30.8.  A step
 // of 9999 tokens of 300 floats (79 workgroups, 1.2 column blocks): 44.6 -> 43.9.
+// Two floats per lane only where that makes fewer column blocks: rows of up to 64
+// floats are one block either way, and slower so (700000 tokens of 10 floats, one
+// id 153 -> 162 us, Zipf 139 -> 148; of 66 floats, two blocks or one, 205 -> 200).
 constexpr int kReduceMinGroups = 150;
 int reduce_vec(int nred, int D, const void* grad, bool grad_bf16, const float* uniq_grad) {
   const size_t elem = grad_bf16 ? 2 : 4;
   for (int vec = 4; vec >= 2; vec /= 2) {
-    if (D % vec != 0 || reinterpret_cast<uintptr_t>(grad) % (vec * elem) != 0 ||
+    if (D % vec != 0 || (vec == 2 && D <= kWave) || reinterpret_cast<uintptr_t>(grad) % (vec * elem) != 0 ||
         reinterpret_cast<uintptr_t>(uniq_grad) % (vec * sizeof(float)) != 0)
       continue;
     // full column blocks (a block of few columns loads little)

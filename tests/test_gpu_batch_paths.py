@@ -202,7 +202,7 @@ def test_column_pack_counts_and_tiles(cap, R, D, P):
 
 # -------------------------------------------------------------------- reduction
 @pytest.mark.parametrize("T,D", [(2100, 4), (2100, 6), (2100, 130), (2500, 516), (9000, 258), (9601, 128), (19100, 64),
-                                 (19300, 64)])
+                                 (19300, 64), (40000, 62), (40000, 64), (40000, 66)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_reduction_vector_widths(T, D, bf16):
     # one, two and four floats per lane (few workgroups take narrower vectors), rows that only two
