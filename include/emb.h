@@ -100,9 +100,10 @@ int emb_gather(const float *table, int64_t V, int32_t D, const int32_t *ids,
  * (sorted position order, in chunks of 32 tokens, then an ordered combine of
  * the chunk partials; a batch of at most 2048 tokens is summed in plain
  * sorted position order): results are bitwise reproducible run to run.
- * For large batches (more than 655360 tokens) workgroups of one launch hand
- * prefix sums to each other (decoupled look-back); every wait is bounded and
- * a timeout sets EMB_DEV_STALLED.
+ * In large batches (more than 655360 tokens; more than 131072 where the keys
+ * have at most 9 bits) workgroups of one launch hand prefix sums to each other
+ * (decoupled look-back); every wait is bounded and a timeout sets
+ * EMB_DEV_STALLED.
  * workspace: device memory of at least
  * emb_grad_coalesce_workspace_bytes(T, V, D, grad_dtype) bytes, 256-byte
  * aligned; its contents on entry do not matter.

@@ -72,8 +72,8 @@ struct BucketCfg {
 // past Few's range the copies of one-key buckets by workgroups that each sum
 // all tiles' starts cost more than a launch (524288 Zipf(1.3) tokens: 107 us
 // against 65 with the copy kernel).
-using Few = BucketCfg<8, 512, 2, 1 << 17, false>;
-using Mid = BucketCfg<9, 512, 4, 1 << 18, true>;
+using Few = BucketCfg<8, 512, 2, kBucketFewTokens, false>;
+using Mid = BucketCfg<9, 512, 4, kBucketMidTokens, true>;
 using Many = BucketCfg<10, 1024, 4, kBucketMaxTokens, true>;
 // They fit beside T words in 3/2 words per token, rounded up to 1024 tokens.
 static_assert(Few::words(1) + 1 <= 1536 && Few::words(Few::kMaxTokens) <= Few::kMaxTokens / 2 &&

@@ -10,8 +10,8 @@
 //     an id (heads) in each run of 128 sorted tokens.  Tokens whose id (or
 //     owner) is out of range take no part: they are not in the sorted sequence,
 //     which holds the n_valid tokens that do.  Batches of at most 655360 tokens
-//     take the bucket sort (bucket_sort.hip: two or three launches); larger
-//     ones a radix sort:
+//     take the bucket sort (bucket_sort.hip: two launches, three above 131072
+//     tokens); larger ones, and from 131072 on those of one pass, a radix sort:
 //     sort_keys_upsweep: the sort key of every token (owner and next-batch
 //     lookups done once) and the digit histograms of every radix pass at once
 //     (the digit totals do not depend on the order of the keys); it also
@@ -1286,14 +1286,29 @@ CoalesceWs carve(void* base, int T, int D, int T_next, int64_t V) {
   return w;
 }
 
-// Batches the bucket sort takes: all that its buckets (of 4096 tokens at most in
-// LDS) hold with room to spare.  Lookup requests of T tokens, uniform and
-// Zipf(1.3) ids of 2^20 rows, radix -> bucket sort: 300: 27 -> 19 us; 16384:
-// 30.3 -> 20.5 and 30.8 -> 20.4; 65536: 36.0 -> 20.2 and 38.3 -> 22.8; 131072:
-// 44.4 -> 28.2 and 44.5 -> 33.8; 262144: 57 -> 40 and 59 -> 42; 524288: 92 -> 67
-// and 93 -> 65; 655360: 111 -> 75 and 112 -> 67; at 2^20 uniform tokens, where
-// buckets start to overflow, 175 -> 181.
-bool bucket_sorted(int T) { return T <= kBucketMaxTokens; }
+// Batches the bucket sort takes.  Lookup requests of T tokens, uniform and Zipf(1.3)
+// ids of 2^20 rows (24 key bits, three radix passes), radix -> bucket sort: 300: 27 ->
+// 19 us; 16384: 30.3 -> 20.5 and 30.8 -> 20.4; 65536: 36.0 -> 20.2 and 38.3 -> 22.8;
+// 131072: 44.4 -> 28.2 and 44.5 -> 33.8; 262144: 57 -> 40 and 59 -> 42; 524288: 92 -> 67
+// and 93 -> 65; 655360: 111 -> 75 and 112 -> 67.
+// Its end, kBucketMaxTokens: a bucket holds two of the samples' gaps, and one of more
+// than kCap = 4096 tokens is sorted by one workgroup through memory, which adds about
+// 110 us to the call (a bucket of 14000 tokens 320).  Of batches of uniform ids one in
+// 2000 has such a bucket at 131072 tokens, one in 500 at 524288, one in 25 at 655360
+// and nearly all at 2^20.  Above the end a batch without one would still be faster, one
+// with it not: 720896: 118 -> 75; 786432: 128 -> 74 or 185; 917504: 155 -> 71 or 159;
+// 2^20: 175 -> 113 or 186.
+// Keys of one radix pass (up to 9 bits) are faster so past the smallest buckets'
+// range, while the pass's tiles are few more than the CUs (256): lookup requests,
+// radix against bucket sort, 150000 tokens of 100 rows 23 against 29 us, 320000 of
+// 256 rows 32 against 45; 400000, 41 against 48; 450000, 48 each.  Keys of two passes
+// take the bucket sort: 280000 tokens of 4000 rows, uniform 43 against 50, but Zipf
+// 44 against 44, one id 46 against 30, and a merge whose tokens are a tenth there 57
+// against 39.
+constexpr int kOnePassTokens = 256 * 9 / 8 * Narrow::kTile;
+bool bucket_sorted(int T, const RadixPlan& plan) {
+  return T <= kBucketFewTokens || (T <= kBucketMaxTokens && (plan.npass > 1 || T > kOnePassTokens));
+}
 
 // The bucket sort's arrays, in the regions that the radix passes use (at least
 // 1.5 words per token each): the long buckets' keys and its own words share one.
@@ -1384,7 +1399,7 @@ RadixPlan plan_for_call(int64_t V, const CoalesceVariant& var) {
 // in keys_b / vals_b and alternate from keys_a, so the sorted keys and positions
 // are in the buffer the last pass wrote.
 void sorted_arrays(const CoalesceWs& ws, const RadixPlan& plan, int T, const uint32_t** skeys, const int32_t** spos) {
-  const bool odd = bucket_sorted(T) || plan.npass % 2 == 1;
+  const bool odd = bucket_sorted(T, plan) || plan.npass % 2 == 1;
   *skeys = odd ? ws.keys_a : ws.keys_b;
   *spos = odd ? ws.vals_a : ws.vals_b;
 }
@@ -1441,7 +1456,7 @@ hipError_t sort_chain(const int32_t* ids, int T, int64_t V, int D, const Coalesc
   }
   // a small batch is sorted and summed by one kernel of the reduction half
   if (!full && small_batch(T, ks)) return hipGetLastError();
-  if (bucket_sorted(T)) {
+  if (bucket_sorted(T, plan)) {
     BucketWs bws = bucket_ws(ws);
     bws.zero_counts = zero_counts;
     bws.P = var.P;
@@ -1611,7 +1626,7 @@ hipError_t launch_lookup_request(const int32_t* ids, int T, int64_t V, const int
   // launch of their own for them cost more (2000 tokens: 19.5 -> 16 to 18 us a call;
   // 65536: 20.7 -> 18.8), and so did an addition per wave and owner (1024 of them on
   // one cache line: 29 us at 65536)
-  const bool counted = bucket_sorted(T);
+  const bool counted = bucket_sorted(T, plan);
   hipLaunchKernelGGL(request_kernel, dim3(nred), dim3(kRedTile), 0, stream, kin, vin, ws.n_valid, T, ws.tile_heads, ks,
                      ids, req_ids, req_offsets, counted ? req_counts : nullptr, num_unique, inverse);
   if (!counted)

@@ -67,18 +67,21 @@ struct BucketWs {
   uint16_t* starts;                 // per tile: where each bucket starts in it, and its token count
   int32_t* heavy_dst;               // per tile: where its tokens of each one-key bucket go
 };
+// The most tokens of the bucket sort's three configurations.
+constexpr int kBucketFewTokens = 1 << 17, kBucketMidTokens = 1 << 18, kBucketMaxTokens = 5 << 17;
 // The vertical split's set of next ids is built in LDS by each workgroup of the
 // bucket sort's first kernel (a bit per row), up to these sizes: two launches
 // (clear and insert, 6.5 us with their gaps) against reading the ids once per
-// tile, which costs as much at 16384 to 20000 ids (split calls, 4096 tokens and
-// next ids: 30.5 -> 27.1 us; 16384: 30.5 -> 28.5, but 44.5 -> 44.8 with rows of
-// 4 KB and ids that are not in the caches; 25000: 29.9 -> 31.3).
+// tile (split calls, 4096 tokens and next ids: 30.5 -> 27.1 us; 25000: 29.9 ->
+// 31.3).  At 16384 ids it depends on whether they are in the caches, where a
+// training step's next ids, just copied, need not be: 30.5 -> 28.5 us, but 44.5 ->
+// 44.8 with rows of 4 KB that have passed through since; so half of that.  The
+// set's up to 32 KB of LDS are measured with the smallest configuration only.
 constexpr int64_t kLdsNextRows = 1 << 18;
 constexpr int kLdsNextIds = 1 << 13;
 inline bool bucket_next_in_lds(int64_t V, int T, int T_next) {
-  return T <= 1 << 17 && V <= kLdsNextRows && T_next <= kLdsNextIds;
+  return T <= kBucketFewTokens && V <= kLdsNextRows && T_next <= kLdsNextIds;
 }
-constexpr int kBucketMaxTokens = 5 << 17;  // the most tokens the bucket sort takes
 // Sorts T (1 .. kBucketMaxTokens) tokens by (key, position); key_bits: bits of
 // the keys; words: 3/2 words per token (T rounded up to 1024) less T words.
 void launch_bucket_sort(const int32_t* ids, int T, const KeySpec& ks, int key_bits, BucketWs ws, uint32_t* words,

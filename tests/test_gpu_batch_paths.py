@@ -99,6 +99,14 @@ def test_batch_sizes(T, s):
     check_by_owner(ids, grads_for(T, T, D, 0.01), V, own, P)
 
 
+@pytest.mark.parametrize("V", [1, 256, 512, 513])
+@pytest.mark.parametrize("T", [131072, 131073, 200000, 442368, 442369])
+def test_one_pass_keys(V, T):
+    # the edges of the range in which keys of one pass take the radix sort
+    ids = ids_for("uniform", V + T, T, V)
+    check_coalesce(ids, grads_for(T, T, 2, 0.01), V)
+
+
 @pytest.mark.parametrize("T", [1, 63, 700, 1025, 140000, 270000])
 def test_lookup_request_sizes(T):
     V, P = 40000, 7
