@@ -99,12 +99,62 @@ def test_batch_sizes(T, s):
     check_by_owner(ids, grads_for(T, T, D, 0.01), V, own, P)
 
 
+# ------------------------------------------------------------------- radix sort
+# Keys of at most nine bits above 131072 tokens, and every batch above 655360.  (V, P): the key bits
+# are those of V alone (P = 0: the plain call) or of V and P; the passes in comments.
+RADIX = [(1, 0), (256, 0), (128, 2),                                     # one pass of 8-bit digits
+         (512, 0), (300, 0), (128, 3),                                   # one of 9-bit digits
+         (1024, 0), (65536, 0), (1 << 12, 16),                           # two of 8-bit digits
+         (65537, 0), (1 << 18, 0), (1 << 14, 9),                         # two of 9-bit digits
+         (1 << 24, 0), (1 << 19, 1), (1 << 20, 16),                      # three of 8-bit digits
+         (1 << 25, 0), (1 << 27, 0), (1 << 20, 33),                      # three of 9-bit digits
+         ((1 << 28) - 3, 0), ((1 << 31) - 1, 0), ((1 << 22) - 1, 1024)]  # four of 8-bit digits
+
+
+@pytest.mark.parametrize("V,P", RADIX)
+@pytest.mark.parametrize("T", [655361, 700000])
+def test_radix_passes(V, P, T):
+    law = "zipf" if V < 1 << 22 and T % 2 else "uniform"
+    ids = ids_for(law, V + T, T, V)
+    ids[5::1003] = -1
+    G = grads_for(T, T, 2, 0.01)
+    if P == 0:
+        check_coalesce(ids, G, V)
+    else:
+        check_by_owner(ids, G, V, owners("mod", V, P), P)
+
+
 @pytest.mark.parametrize("V", [1, 256, 512, 513])
 @pytest.mark.parametrize("T", [131072, 131073, 200000, 442368, 442369])
 def test_one_pass_keys(V, T):
     # the edges of the range in which keys of one pass take the radix sort
     ids = ids_for("uniform", V + T, T, V)
     check_coalesce(ids, grads_for(T, T, 2, 0.01), V)
+
+
+@pytest.mark.parametrize("V,P", [(100, 2), (1 << 14, 4), (1 << 20, 7), (1 << 23, 16), ((1 << 22) - 1, 1024)])
+@pytest.mark.parametrize("T", [150000, 655361])
+def test_lookup_request_radix(V, P, T):
+    # requests of radix-sorted tokens (above 131072 those of one pass): offsets first, counts from them
+    ids = ids_for("zipf" if P == 7 else "uniform", V + T, T, V)
+    ids[[0, T // 2, T - 1]] = [-3, V, V + 77]
+    own = owners("rand", V, P, seed=T)
+    own[::13] = P
+    check_request(ids, V, own, P)
+
+
+def test_lookup_request_radix_without_tokens():
+    V, P, T = 1000, 5, 655361
+    check_request(np.full(T, V, np.int32), V, owners("mod", V, P), P)
+
+
+@pytest.mark.parametrize("V,P,T_next", [(60, 2, 700), (50000, 3, 20000), (1 << 20, 16, 700000), ((1 << 24) + 9, 8, 5000),
+                                        ((1 << 21) - 1, 1024, 1)])
+@pytest.mark.parametrize("T", [140000, 655361])
+def test_split_radix(V, P, T, T_next):
+    ids, nxt = ids_for("uniform", V + T, T, V), ids_for("uniform", V + T + 1, T_next, V)
+    nxt[3::11] = -1
+    check_split(ids, nxt, grads_for(T, T, 2, 0.01), V, owners("mod", V, P), P)
 
 
 @pytest.mark.parametrize("T", [1, 63, 700, 1025, 140000, 270000])
@@ -126,10 +176,13 @@ def test_lookup_request_owners_without_requests(used, T):
     check_request(ids, V, owners("mod", V, P), P)
 
 
-@pytest.mark.parametrize("count", [0, 1, 3000, 139999])
-def test_device_count_over_all_samples(count):
-    # a device-side token count: the samples come from the tokens that exist
-    T, V, P, D = 140000, 5000, 3, 4
+@pytest.mark.parametrize("T,V,P,count", [(140000, 5000, 3, c) for c in (0, 1, 3000, 139999)] +
+                         # the radix sort: one pass of 9-bit digits, two of 8, four of 8
+                         [(140000, 100, 3, 77777), (655361, 5000, 3, 0), (655361, 5000, 3, 400000),
+                          (655361, (1 << 22) - 1, 1024, 655360)])
+def test_device_count(T, V, P, count):
+    # a device-side token count: the samples of the bucket sort come from the tokens that exist
+    D = 4
     ids = ids_for("zipf", 3, T, V)
     G = grads_for(3, T, D, 0.01)
     own = owners("mod", V, P)
