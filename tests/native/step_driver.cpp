@@ -4,7 +4,7 @@
 //   step 1: emb_gather, emb_grad_coalesce_by_owner, emb_sparse_adam_apply
 //           (5000 tokens: the multi-kernel coalesce);
 //   step 2: emb_train_step, owner-major, every stage on the one stream
-//           (1500 tokens: the one-workgroup coalesce).
+//           (1500 tokens: the one-launch coalesce).
 // Checks per step: the lookup bit-exact against the oracle's gather of the
 // table as it was before the step; send ids, counts and offsets bit-exact
 // against the oracle's coalesce and pack; each sent row within 1e-5 of the

@@ -1,7 +1,8 @@
 """The coalesce's paths by batch size, at the edges of their tiles, against the oracle: every kernel
 variant of the small batches (512, 1024 and 2048 tokens) with whole, partial and looped column
-slices, vector and scalar rows, and both gradient types; the bucket sort's bucket and tile sizes, and
-the first batch past it; the lookup requests and device-side token counts over the same paths."""
+slices, vector and scalar rows, and both gradient types; the bucket sort's bucket and tile sizes; the
+radix sort's digit widths and pass counts; the lookup requests, the split and device-side token counts
+over the same paths; and the other calls at the edges of their rules on sizes."""
 import numpy as np
 import pytest
 import torch
@@ -66,15 +67,18 @@ LAWS = {"even": (1 << 20, 1 << 20), "bunched": (1 << 20, 300), "few": (1 << 20, 
 
 
 @pytest.mark.parametrize("law", sorted(LAWS))
-@pytest.mark.parametrize("m", [1, 511, 513, 1025, 2049, 4096, 4097, 20000])
-def test_bucket_of_any_size(m, law):
-    # every sampled token holds id 5, so the ids above it fall into one bucket of m tokens: each
-    # variant of the bucket's sort, and the one for buckets that do not fit in LDS
+@pytest.mark.parametrize("T,n,m", [(30000, 512, m) for m in (1, 511, 513, 1025, 2049, 4096, 4097, 20000)] +
+                         [(T, n, m) for T, n in ((140000, 1024), (262144, 1024), (655360, 2048))
+                          for m in (600, 4096, 4097, 20000)])
+def test_bucket_of_any_size(T, n, m, law):
+    # every sampled token (n of the batch) holds id 5, so the ids above it fall into one bucket of m
+    # tokens: each variant of the bucket's sort, and the one for buckets that do not fit in LDS, in each
+    # of the sort's three configurations
     V, top = LAWS[law]
-    T, D = 30000, 4
+    D = 4 if T < 100000 else 1
     rng = np.random.default_rng(m)
     ids = np.full(T, 5, np.int32)
-    free = np.setdiff1d(np.arange(T), sample_tokens(512, T))
+    free = np.setdiff1d(np.arange(T), sample_tokens(n, T))
     at = rng.choice(free, m, replace=False)
     ids[at] = rng.integers(6, min(top, V), m)
     if law == "bunched":
@@ -225,7 +229,7 @@ def test_pack_places(T, D, P):
 
 # ------------------------------------------------------------------------ split
 @pytest.mark.parametrize("T,T_next,V", [
-    (300, 1, 1000), (1000, 2048, 900000), (2048, 2048, 1 << 25), (2000, 2049, 5000),  # small batches
+    (300, 1, 1000), (1000, 2048, 900000), (2048, 2048, 1 << 25), (2000, 2049, 5000), (1500, 3000, (1 << 24) + 5),  # small batches
     (2049, 1, 1 << 18), (5000, 8192, 1 << 18), (5000, 8193, 1 << 18), (5000, 700, (1 << 18) + 1), (3000, 8191, 33),
     (131072, 9000, 40000), (131073, 9000, 40000)])
 @pytest.mark.parametrize("law", ["zipf", "uniform"])

@@ -68,7 +68,7 @@ def check_exchange(send_ids, send_rows, send_offs, P, cap):
 @pytest.mark.parametrize("P,law,D,rule,T", [(1, "zipf", 16, "mod", 3000), (2, "uniform", 64, "mod", 3000),
                                             (4, "zipf", 3, "range", 3000), (16, "uniform", 32, "mod", 3000),
                                             (7, "zipf", 8, "rand", 3000),
-                                            (2, "zipf", 16, "mod", 1000)])  # merge of 1903 of 2000 rows: one workgroup
+                                            (2, "zipf", 16, "mod", 1000)])  # merge of 1903 of 2000 rows: one launch
 def test_exchange_then_merge_equals_coalesce_of_all_tokens(P, law, D, rule, T):
     V = 20000
     sizes = [T - 97 * w for w in range(P)]  # ragged worker batches

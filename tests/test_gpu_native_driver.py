@@ -1,6 +1,6 @@
 """The C ABI from native code, no Python binding and no torch: tests/native/step_driver.cpp runs
 two training steps of one table (the calls one by one through the multi-kernel coalesce, then
-emb_train_step through the one-workgroup coalesce) and checks each against the CPU oracle
+emb_train_step through the one-launch coalesce) and checks each against the CPU oracle
 (lookup bit-exact, send layout bit-exact, sums within the fp32 summation bound, the update on its
 own scale, rows not sent unchanged).  Built by __graft_entry__.build()."""
 import os

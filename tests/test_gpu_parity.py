@@ -1,5 +1,5 @@
 """Parity of each C ABI call with the oracle at sizes the oracle finishes in
-seconds: several sort tiles (1024 keys, 1536 above 32768 tokens) and reduction chunks (32 tokens) with
+seconds: several tiles of the sorts and reduction chunks (32 tokens) with
 ragged tails, every gradient width path (vector and scalar), bf16 gradients,
 hot rows spanning many chunks, empty and degenerate inputs."""
 import numpy as np
@@ -62,39 +62,39 @@ def test_gather_empty():
 # -------------------------------------------------------------------- coalesce
 @pytest.mark.parametrize("law,V,T,D", [
     ("zipf", 1000, 512, 64),         # the tiny workload's shape
-    ("zipf", 5000, 2048, 8),         # the most tokens of the one-workgroup path
-    ("zipf", 5000, 3072, 8),         # exactly three sort tiles
-    ("zipf", 5000, 2049, 3),         # two whole sort tiles and one key, scalar width path
-    ("uniform", 1 << 20, 10000, 16),  # 20 key bits: three passes of 7 bits
+    ("zipf", 5000, 2048, 8),         # the most tokens of the one-launch path
+    ("zipf", 5000, 3072, 8),         # exactly three tiles of the bucket sort
+    ("zipf", 5000, 2049, 3),         # two whole tiles and one token, scalar width path
+    ("uniform", 1 << 20, 10000, 16),  # 20 key bits
     ("zipf", 32768, 25000, 65),      # odd width (scalar path), many chunks
-    ("zipf", 300, 4001, 256),        # very heavy duplication; 9 key bits: one 9-bit pass
+    ("zipf", 300, 4001, 256),        # very heavy duplication; 9 key bits
     ("uniform", 50, 33, 1),          # one chunk + 1, D = 1
-    ("zipf", 1, 777, 4),             # V = 1: every key 0 (one pass), one segment over 25 chunks
-    ("uniform", 5_000_000, 9000, 8),  # 23 key bits: three 8-bit passes
-    ("uniform", (1 << 31) - 1, 5000, 4),  # 31 key bits: four passes
-    ("zipf", 65535, 12000, 16),      # 16 key bits: two 8-bit passes
-    ("zipf", 65537, 12000, 16),      # 17 key bits: two 9-bit passes
-    ("uniform", (1 << 22) - 1, 20000, 4),  # 22 key bits
-    ("uniform", 1 << 25, 20000, 4),  # 25 key bits: three 9-bit passes (9, 9, 7)
-    ("uniform", (1 << 27) - 1, 9000, 4),  # 27 key bits: three 9-bit passes
-    # batches of at most 2048 tokens (the one-workgroup path): four 8-bit passes in LDS, one
-    # segment of all 2048 tokens, a hot row over many of them, a single token
+    ("zipf", 1, 777, 4),             # V = 1: every key 0, one segment of the whole batch
+    # the bucket sort with keys of 16 to 31 bits (the radix sort's digit widths and pass counts:
+    # test_gpu_batch_paths.py)
+    ("uniform", 5_000_000, 9000, 8),
+    ("uniform", (1 << 31) - 1, 5000, 4),
+    ("zipf", 65535, 12000, 16),
+    ("zipf", 65537, 12000, 16),
+    ("uniform", (1 << 22) - 1, 20000, 4),
+    ("uniform", 1 << 25, 20000, 4),
+    ("uniform", (1 << 27) - 1, 9000, 4),
+    # batches of at most 2048 tokens (the one-launch path): four passes in LDS, one segment of all
+    # 2048 tokens, a hot row over many of them, a single token
     ("uniform", (1 << 31) - 1, 2000, 4),
     ("zipf", 1, 2048, 4),
     ("zipf", 300, 1999, 256),
     ("uniform", 7, 1, 5),
-    # the largest batch of 1024-key sort tiles, and the smallest of 1536-key tiles (ragged: 21 whole
-    # tiles and 513 keys)
+    # more tiles of the bucket sort, whole and ragged
     ("uniform", 1 << 20, 32768, 4),
     ("zipf", 1 << 20, 32769, 4),
-    # 1536-key tiles with 9-bit digits: 17 key bits (two passes), 26 key bits (three passes), one
-    # and a ragged tail of 1535 keys
     ("zipf", 65537, 49151, 8),
     ("uniform", (1 << 26) - 3, 40000, 4),
-    # more than 1024 reduction workgroups: the head counts are scanned once by their own kernel
+    # more than 1024 reduction workgroups, whose earlier head counts take more than one round of loads;
+    # 512 buckets
     ("zipf", 1 << 20, 200000, 8),
     ("uniform", 1 << 18, 131073, 4),
-    # two million tokens: 1366 sort tiles to look back over, 16384 reduction workgroups
+    # two million tokens, radix-sorted: 1366 sort tiles to look back over, 16384 reduction workgroups
     ("uniform", 1 << 22, 1 << 21, 4),
     ("zipf", 1 << 20, (1 << 21) + 77, 4),
 ])

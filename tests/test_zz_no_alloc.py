@@ -4,7 +4,7 @@ a workspace the caller allocates: both run the same kernels in the same order, s
 required bit for bit equal (ids, segment offsets, rows, counts, offsets, the unique count, the
 device status).  Three calls in a row on the same array, each smaller than the one before (the
 multi-kernel path at the low-duplication stress shape, then a narrower batch, then one small enough
-for the one-workgroup path), so that what the first call left in the array cannot leak into the
+for the one-launch path), so that what the first call left in the array cannot leak into the
 later ones.  Called through the C ABI."""
 import ctypes
 
@@ -52,7 +52,7 @@ def call(ids, G, V, own, P, noalloc):
 SHAPES = [
     ("uniform", 1 << 20, 65536, 256, 16, "mod"),   # the low-duplication stress shape
     ("zipf", 32768, 20000, 64, 4, "range"),        # smaller: fewer tokens, narrower rows
-    ("zipf", 5000, 1500, 32, 8, "mod"),            # one-workgroup path
+    ("zipf", 5000, 1500, 32, 8, "mod"),            # one-launch path
 ]
 
 
