@@ -130,17 +130,20 @@ def _check(status: int, what: str):
 # as plain integers (the c_void_p argument types take them; an object each cost 0.1 us more, 28 a
 # training step), and the current stream's handle is asked for directly (torch.cuda.current_stream()
 # builds a Stream object: 2.9 us a call).  Host time of a step of 512 tokens (lookup, owner-major
-# coalesce, update): 30.1 -> 20.3 us.
-_current_device = torch._C._cuda_getDevice
-_current_raw_stream = torch._C._cuda_getCurrentRawStream
+# coalesce, update): 30.1 -> 20.3 us.  The direct way goes through two private names of torch; where a
+# torch lacks them, the public call serves.
+try:
+    from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
+
+    def _stream(stream):
+        return _cuda_getCurrentRawStream(_cuda_getDevice()) if stream is None else stream.cuda_stream
+except ImportError:
+    def _stream(stream):
+        return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _ptr(t):
     return None if t is None else t.data_ptr()
-
-
-def _stream(stream):
-    return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
 def _dtype_code(t):

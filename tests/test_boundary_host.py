@@ -4,6 +4,8 @@ is enqueued (no device memory is touched by these calls)."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -31,6 +33,20 @@ def test_library_exports_every_declared_symbol():
     for name in declared_functions():
         assert hasattr(lib, name), f"{name} declared in emb.h but not exported"
         assert name in emb.SIGNATURES, f"{name} has no binding signature"
+
+
+def test_binding_without_torchs_private_stream_calls():
+    # a torch that lacks them: the package imports, and the current stream comes from the public call
+    code = ("import torch\n"
+            "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    delattr(torch._C, n)\n"
+            "import paper_2110_09132_amd as emb\n"
+            "class S: cuda_stream = 4711\n"
+            "torch.cuda.current_stream = lambda: S()\n"
+            "class T: cuda_stream = 4712\n"
+            "assert emb._stream(None) == 4711 and emb._stream(T()) == 4712\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
 
 
 def test_status_strings_and_version():
