@@ -1,9 +1,12 @@
-// Sort of a batch's tokens by (key, position) in two launches, for batches of
-// up to kBucketMaxTokens tokens (a sample sort; Frazer & McKellar 1970).
+// Sort of a batch's tokens by (key, position) for batches of up to
+// kBucketMaxTokens tokens (a sample sort; Frazer & McKellar 1970), in two
+// launches up to kBucketFewTokens tokens and three above.  The figures here are
+// those of the smallest of the three configurations (BucketCfg, below).
 //
-//  1. bucket_split: every tile of 1024 tokens forms its keys, takes the same
-//     512 sample tokens of the batch, sorts their keys and keeps every second
-//     one as a splitter (256 buckets of about equal size whatever the keys'
+//  1. bucket_split: every tile of 1024 tokens (2048 or 4096 in the larger
+//     configurations) forms its keys, takes the same 512 (1024, 2048) sample
+//     tokens of the batch, sorts their keys and keeps every second one as a
+//     splitter (256, 512 or 1024 buckets of about equal size whatever the keys'
 //     distribution; a key that fills a bucket by itself gets one of its own).
 //     It then orders its tokens by bucket, stably, into its own part of a
 //     scratch array and leaves where each bucket starts.
@@ -14,10 +17,12 @@
 //     first tokens of each id for the reduction.  Buckets of one key need no
 //     sort and can be long (a hot id): one more workgroup per tile copies its
 //     tokens of those buckets.
+//  3. bucket_copy, in the larger configurations: those copies in a launch of
+//     their own, to the places that the buckets' workgroups have left.
 // The result is the stable order by key, whatever the samples: they only
 // decide how evenly the work is spread.
 //
-// Both kernels are bound by latency (a chain of memory round trips, LDS steps
+// The kernels are bound by latency (a chain of memory round trips, LDS steps
 // and barriers; 64 tiles and 256 buckets for 65536 tokens), so what counts is
 // how many dependent launches and round trips there are.  The radix sort of
 // the same keys (key build, three passes, head count) takes five launches, its
@@ -131,7 +136,10 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&v)[IT], uint32_t* buf) {
 
 // Sample i's token: one at a scattered place of each of n equal shares
 // of the batch (an even stride could meet a period of the tokens, such as the
-// first token of every sentence).
+// first token of every sentence).  The scattering is the first shift,
+// multiplication and shift of xxHash32's final mix (Y. Collet's published
+// specification; the multipliers are its primes 1 and 2) of i * prime 1 plus a
+// constant, the low half of 2^64 / golden ratio.
 __device__ __forceinline__ int sample_token(int i, int n, int Tc) {
   const int lo = static_cast<int>(static_cast<long long>(i) * Tc / n);
   const int hi = static_cast<int>(static_cast<long long>(i + 1) * Tc / n);
@@ -406,9 +414,9 @@ __device__ __forceinline__ void sort_bucket(BucketLds<C>& l, const BucketWs& ws,
   if (tid < kHeadWords && l.hh[tid] != 0 && first + tid <= (T - 1) / kRedTile) atomicAdd(&ws.tile_heads[first + tid], l.hh[tid]);
 }
 
-// A bucket of more than kCap tokens (only when the samples miss most of the
-// batch's keys): an LSD radix sort between the bucket's places in the result
-// and in the scratch arrays, by this workgroup alone.
+// A bucket of more than kCap tokens (rare: bucket_sorted in coalesce.hip says how
+// rare, and what it costs): an LSD radix sort between the bucket's places in the
+// result and in the scratch arrays, by this workgroup alone.
 template <class C>
 __device__ __forceinline__ void sort_long_bucket(BucketLds<C>& l, const BucketWs& ws, int T, int base, int n, uint32_t lo,
                                               int wbits) {

@@ -1101,11 +1101,11 @@ __global__ __launch_bounds__(NT) void small_coalesce_kernel(
 // Lookup requests of the row-wise partition, from the owner-major sorted
 // tokens: one thread per sorted token.  A token heads its id when its key
 // differs from the previous one; its unique index u is the number of heads up
-// to it (earlier workgroups' counts from seg_count, then the workgroup's own)
-// minus one.  Heads write req_ids[u] and the owner-group starts; every sorted
-// token writes inverse[its position] = u.  Token t = the same thread index
-// writes inverse[t] = -1 when it takes no part (those tokens are not in the
-// sorted sequence).
+// to it (earlier workgroups' counts from the sort, bucket_sort or seg_count, then
+// the workgroup's own) minus one.  Heads write req_ids[u] and the owner-group
+// starts; every sorted token writes inverse[its position] = u.  Token t = the same
+// thread index writes inverse[t] = -1 when it takes no part (those tokens are not
+// in the sorted sequence).
 __global__ __launch_bounds__(kRedTile) void request_kernel(const uint32_t* __restrict__ skeys,
                                                            const int32_t* __restrict__ spos,
                                                            const uint32_t* __restrict__ n_valid, int T,
@@ -1187,8 +1187,8 @@ __global__ __launch_bounds__(kRedTile) void request_kernel(const uint32_t* __res
   }
 }
 
-// Per-owner request counts from the offsets (one workgroup, P <= 1024); with
-// an empty batch it writes the empty result first.
+// Per-owner request counts from the offsets (one workgroup, P <= 1024), after the
+// radix sort; with an empty batch it writes the empty result first.
 __global__ __launch_bounds__(1024) void request_counts_kernel(int32_t* __restrict__ req_offsets,
                                                               int32_t* __restrict__ req_counts,
                                                               int32_t* __restrict__ num_unique, int P, int empty) {
