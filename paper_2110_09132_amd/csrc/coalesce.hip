@@ -1299,12 +1299,14 @@ CoalesceWs carve(void* base, int T, int D, int T_next, int64_t V) {
 // with it not: 720896: 118 -> 75; 786432: 128 -> 74 or 185; 917504: 155 -> 71 or 159;
 // 2^20: 175 -> 113 or 186.
 // Keys of one radix pass (up to 9 bits) are faster so past the smallest buckets'
-// range, while the pass's tiles are few more than the CUs (256): lookup requests,
-// radix against bucket sort, 150000 tokens of 100 rows 23 against 29 us, 320000 of
-// 256 rows 32 against 45; 400000, 41 against 48; 450000, 48 each.  Keys of two passes
-// take the bucket sort: 280000 tokens of 4000 rows, uniform 43 against 50, but Zipf
-// 44 against 44, one id 46 against 30, and a merge whose tokens are a tenth there 57
-// against 39.
+// range, while the pass's tiles are few more than the CUs (256): lookup requests of
+// uniform ids, radix against bucket sort, 150000 tokens of 100 rows 23 against 25 us,
+// of 256 rows 24 against 29; 320000 of 256 rows 32 against 45; 400000, 41 against 46;
+// 442368, 44 against 48, but 100 rows 43 each.  One id alone is faster in the bucket
+// sort (320000 tokens 32 against 30, 442368 43 against 32), which is the price.  Keys
+// of two passes take the bucket sort: 280000 tokens of 4000 rows, uniform 43 (radix) against 50, but Zipf 44 against 44, 300000 tokens of
+// one id 46 against 30, and a merge of 300000 rows of which a tenth is there (30000
+// table rows, 8 owners) 73 against 53.
 constexpr int kOnePassTokens = 256 * 9 / 8 * Narrow::kTile;
 bool bucket_sorted(int T, const RadixPlan& plan) {
   return T <= kBucketFewTokens || (T <= kBucketMaxTokens && (plan.npass > 1 || T > kOnePassTokens));

@@ -142,8 +142,8 @@ constexpr int kPackUnits = 512;
 // Half a tile has half as long a run per owner, and a wave stores a run at a time:
 // past about 12 owners the runs leave most of a wave's lanes idle.  Calls with 1024 ->
 // 512 units, from HBM / from the caches:
-//   up to 12 owners  8000 rows of 4 KB, 8 owners 16.0 -> 15.6 / 11.4 -> 12.4 us; 30000,
-//                    48.9 -> 46.3 / 37.2 both; 3000 of 1 KB, 8 owners 5.5 -> 4.5
+//   up to 12 owners  8000 rows of 4 KB, 8 owners 16.0 -> 15.6 / 11.4 -> 12.4 us; 30000
+//                    from HBM 48.9 -> 46.3; 3000 of 1 KB, 8 owners 5.5 -> 4.5
 //   16 owners        8000 of 4 KB 16.1 -> 17.0 / 12.2 -> 14.5; but few workgroups, 3000
 //                    of 1 KB 5.8 -> 5.1, and much data, 30000 of 4 KB 49.7 -> 47.0
 //   32 owners        1000 of 1 KB 6.3 -> 5.4; 16000 of 4 KB 31.5 -> 35.3
